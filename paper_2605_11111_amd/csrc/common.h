@@ -190,4 +190,59 @@ __device__ __forceinline__ void lds_add_u32(uint32_t addr, uint32_t v)
     asm volatile("ds_add_u32 %0, %1" ::"v"(addr), "v"(v) : "memory");
 }
 
+// Eight binary32 values as three bf16 vectors whose sum is exactly the values
+// (8 + 8 + 8 significant bits): v = hi + mid + lo, each part the nearest bf16 of
+// what the parts before it leave. A product of two such triples keeps the six
+// part products that are not below the rounding of a binary32 product
+// (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi), each exact in binary32.
+// A value whose parts would not be finite (infinity, NaN, or one that rounds up
+// to infinity) takes the slow path: finite ones are cut by truncation, the
+// others become (sign, 0, v), so that v meets the other factor's hi part alone
+// and a product is infinite or NaN exactly where the binary32 product is.
+__device__ __forceinline__ void split_bf16x3(const float (&v)[8], uint4& hi, uint4& mid, uint4& lo)
+{
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_s;
+    uint32_t h[4], m[4], l[4];
+    float rest = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float a = v[2 * i], b = v[2 * i + 1];
+        h[i] = __builtin_bit_cast(uint32_t, bf16x2_s{__bf16(a), __bf16(b)});
+        const float a1 = a - __uint_as_float(h[i] << 16), b1 = b - __uint_as_float(h[i] & 0xFFFF0000u);
+        m[i] = __builtin_bit_cast(uint32_t, bf16x2_s{__bf16(a1), __bf16(b1)});
+        const float a2 = a1 - __uint_as_float(m[i] << 16), b2 = b1 - __uint_as_float(m[i] & 0xFFFF0000u);
+        l[i] = __builtin_bit_cast(uint32_t, bf16x2_s{__bf16(a2), __bf16(b2)});
+        rest += a2 + b2;
+    }
+    if (!(__builtin_fabsf(rest) < 1.f)) {  // NaN where a part was not finite; a tail of 1 or more is cut the same way
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            uint32_t p[2][3];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const float x = v[2 * i + e];
+                const uint32_t u = __float_as_uint(x);
+                if ((u & 0x7F800000u) == 0x7F800000u) {
+                    p[e][0] = 0x3F80u | ((u >> 16) & 0x8000u);
+                    p[e][1] = 0u;
+                    p[e][2] = (u & 0x7FFFFFu) ? 0x7FC0u : (u >> 16);
+                } else {
+                    const float r1 = x - __uint_as_float(u & 0xFFFF0000u);
+                    const uint32_t u1 = __float_as_uint(r1);
+                    const float r2 = r1 - __uint_as_float(u1 & 0xFFFF0000u);
+                    p[e][0] = u >> 16;
+                    p[e][1] = u1 >> 16;
+                    p[e][2] = __float_as_uint(r2) >> 16;
+                }
+            }
+            h[i] = p[0][0] | (p[1][0] << 16);
+            m[i] = p[0][1] | (p[1][1] << 16);
+            l[i] = p[0][2] | (p[1][2] << 16);
+        }
+    }
+    hi = make_uint4(h[0], h[1], h[2], h[3]);
+    mid = make_uint4(m[0], m[1], m[2], m[3]);
+    lo = make_uint4(l[0], l[1], l[2], l[3]);
+}
+
 }  // namespace shardconv

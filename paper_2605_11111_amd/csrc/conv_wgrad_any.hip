@@ -1,0 +1,1039 @@
+// Weight gradient of any shape (kernel, stride, channels, type, folded halo) on
+// v_mfma_f32_32x32x16_bf16: dW[co][ci][t] = sum_v dy[v][co] * tile[v*S + t - pad][ci]
+// as a split-K implicit GEMM with M = 32 output channels, N = 32 input channels
+// of one tap, K = output voxels.
+//
+//  * A workgroup of eight waves (two per SIMD) owns WCO co tiles, a group of
+//    taps (rows of one kd plane, at most nine taps) and nci ci tiles; a "unit" is
+//    one (ci tile, tap). It sweeps a contiguous range of output bricks. A wave
+//    keeps the NU units of its co tile in registers; the waves left over split
+//    the brick's K steps (KS ways) and are summed through LDS at the end, so a
+//    workgroup writes one partial. wgrad_reduce adds the partials in a fixed
+//    order: results are bitwise repeatable.
+//  * A brick's dy and the input voxels that the group's taps meet are staged
+//    channels-last in LDS, 64 bytes (32 channels) per voxel, and read with
+//    ds_read_b64_tr_b16: lane i of a 16-lane group addresses voxel k0 + i / 4 at
+//    channels 4 (i % 4).., lane j receives channel j of the four voxels. Every
+//    lane addresses its own voxel, so a tap is one more offset and any brick
+//    shape works.
+//  * Along a strided axis the staged rows are grouped by residue modulo the
+//    stride (only residues that a tap meets are staged): for every tap,
+//    consecutive outputs read consecutive voxels, and a transposed read covers
+//    256 contiguous bytes (all banks, once) at any stride.
+//  * bf16 bricks are staged by direct global->LDS loads into two or three
+//    buffers (three where they fit: a brick's products take about as long as a
+//    load's latency). binary32 bricks go through registers (loads of brick
+//    b + 2 in flight while brick b multiplies) into two buffers; waves 0-3 write
+//    brick b + 1 and then multiply, waves 4-7 the other way round, so that a
+//    SIMD's two waves overlap the split with MFMAs. One barrier per brick.
+//  * The SLOW variants take folded halos and channels that are not whole aligned
+//    vectors: bf16 bricks that touch a folded margin load each voxel from its own
+//    buffer with per-lane addresses; ragged channels, and binary32 bricks of
+//    a folded call, are staged unit by unit through registers.
+//  * binary32 data is split into three bf16 parts while staging
+//    (split_bf16x3) and multiplied by six MFMAs per product: 192 cycles per 16
+//    K values against 512 on v_mfma_f32_32x32x2_f32, with fewer roundings (one
+//    per 16 products of a part pair instead of one per two).
+#include <algorithm>
+#include <type_traits>
+
+#include "common.h"
+#include "internal.h"
+
+#define SC_LDSY(p) ((__attribute__((address_space(3))) void*)(p))
+#define SC_INLINE __attribute__((always_inline))
+
+namespace shardconv {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_y;
+typedef __attribute__((ext_vector_type(4))) short s16x4_y;
+typedef __attribute__((ext_vector_type(16))) float f32x16_y;
+
+namespace {
+
+constexpr int kThreadsA = 512;
+constexpr int kMaxTaps = 9;      // taps per group
+constexpr int kRedUnits = 4;     // units per round of the K-split sum (8 waves x 4 KiB each)
+constexpr uint32_t kNone = 0xFFFFFFFFu;
+
+struct AnyArgs {
+    const char* tile;
+    const char* dy;
+    float* part;
+    int64_t xbatch, ybatch;            // bytes per batch item
+    uint32_t xplane, xrow, yplane, yrow;  // bytes (a brick's span is below 2^31)
+    int32_t cin, cout;
+    int32_t P[3], O[3], S[3], pad[3];
+    int32_t lb1, lb2, lv, V;           // log2 of the brick's H and W extents and of its voxels
+    int32_t BO[3], NB[3];
+    int32_t NS[3];                     // staged rows per axis
+    int32_t KG[3], NG[3];              // taps per group and groups, per axis
+    int32_t nxs;                       // staged voxels per ci tile
+    int32_t utoff[2 * kMaxTaps];       // per unit: byte offset of its (ci tile, tap) in the staged input
+    int32_t nci, tpg, nmb, ncb, ntg, nsplit;
+    int32_t nbricks;
+    int32_t stageb, dy_off, xtab_off;  // LDS layout, bytes
+    int32_t nbuf;                      // bf16: stage buffers
+    int32_t xvec, dvec;
+    Fold fold;
+};
+
+// Rows along one axis that KG taps at stride S meet for BO outputs, grouped by
+// residue: output o at tap k reads slot start(k % S) + o + k / S.
+__host__ __device__ inline int slot_start(int BO, int KG, int S, int r)
+{
+    int s = 0;
+    for (int q = 0; q < r; ++q) s += q < KG ? BO + (KG - 1 - q) / S : 0;
+    return s;
+}
+__host__ __device__ inline int slot_count(int BO, int KG, int S) { return slot_start(BO, KG, S, S < KG ? S : KG); }
+__host__ __device__ inline int slot_of_tap(int BO, int KG, int S, int k)
+{
+    return slot_start(BO, KG, S, k % S) + k / S;
+}
+// the row (relative to the first output's first tap) of slot s
+__host__ __device__ inline int slot_row(int BO, int KG, int S, int s)
+{
+    int r = 0;
+    for (;;) {
+        const int n = BO + (KG - 1 - r) / S;
+        if (s < n) return s * S + r;
+        s -= n;
+        ++r;
+    }
+}
+
+// Wait until at most n vector-memory operations of this wave are outstanding
+// (n uniform; rounded down to a multiple of four, at most eight).
+__device__ __forceinline__ void wait_vm_dyn(int n)
+{
+    if (n >= 8)
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    else if (n >= 4)
+        asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+    else
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// The wave's LDS operations are done; barrier.
+__device__ __forceinline__ void wait_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// A 32-bit LDS word, waited for in the same block.
+__device__ __forceinline__ uint32_t lds_read_u32(uint32_t addr)
+{
+    uint32_t v;
+    asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(addr) : "memory");
+    return v;
+}
+
+// XU, DU: at most this many 8-channel staging units of input and dy per thread
+// (binary32 keeps them in registers, next to 16 NU accumulator registers);
+// R: 16-byte registers per unit; SU: units in flight per thread in stage_slow
+template <typename T, int NU>
+struct AnyT;
+template <int NU>
+struct AnyT<bf16_t, NU> {
+    static constexpr int PARTS = 1, XU = 6, DU = 4, R = 1, SU = 1;
+};
+template <int NU>
+struct AnyT<float, NU> {
+    static constexpr int PARTS = 3, XU = NU <= 5 ? 4 : 2, DU = NU <= 5 ? 2 : 1, R = 2, SU = 2;
+};
+
+template <typename T, int NU, int WCO, int WU, bool SLOW>
+__global__ __launch_bounds__(kThreadsA, 1) void wgrad_any(AnyArgs a)
+{
+    using C = AnyT<T, NU>;
+    constexpr int PARTS = C::PARTS, R = C::R;
+    constexpr int KS = 8 / (WCO * WU);
+    constexpr int ESZ = int(sizeof(T));
+    constexpr bool DMA = PARTS == 1;
+    extern __shared__ uint4 lds4[];
+    char* lds = reinterpret_cast<char*>(lds4);
+    const uint32_t lds0 = lds_addr(lds);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wco = wave % WCO, wu = (wave / WCO) % WU, ks0 = wave / (WCO * WU);
+
+    // group innermost: the workgroups of an XCD that sweep the same bricks run together
+    const uint32_t L = uint32_t(xcd_remap(blockIdx.x, gridDim.x));
+    const uint32_t groups = uint32_t(a.nmb) * a.ncb * a.ntg;
+    const uint32_t split = L / groups, grp = L - split * groups;
+    const int tg = int(grp % uint32_t(a.ntg)), cb = int(grp / uint32_t(a.ntg)) % a.ncb,
+              mb = int(grp / (uint32_t(a.ntg) * a.ncb));
+    const int g2 = tg % a.NG[2], g1 = (tg / a.NG[2]) % a.NG[1], g0 = tg / (a.NG[2] * a.NG[1]);
+    const int k0[3] = {g0 * a.KG[0], g1 * a.KG[1], g2 * a.KG[2]};
+    const int ci0 = cb * a.nci * 32, co0 = mb * WCO * 32;
+    const int br0 = int(int64_t(split) * a.nbricks / a.nsplit), br1 = int(int64_t(split + 1) * a.nbricks / a.nsplit);
+
+    // offsets of this wave's units in the staged input
+    const int xps = a.nxs * 64;  // bytes of one part of one ci tile
+    int toff[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) toff[u] = a.utoff[wu * NU + u];
+
+    // LDS table: a slot's packed row coordinates
+    uint32_t* xtab = reinterpret_cast<uint32_t*>(lds + a.xtab_off);
+    for (int sl = tid; sl < a.nxs; sl += kThreadsA) {
+        const int s01 = sl / a.NS[2], s2 = sl - s01 * a.NS[2], s0 = s01 / a.NS[1], s1 = s01 - s0 * a.NS[1];
+        xtab[sl] = (uint32_t(slot_row(a.BO[0], a.KG[0], a.S[0], s0)) << 20) |
+                   (uint32_t(slot_row(a.BO[1], a.KG[1], a.S[1], s1)) << 10) |
+                   uint32_t(slot_row(a.BO[2], a.KG[2], a.S[2], s2));
+    }
+    __syncthreads();
+
+    // this thread's staging units (brick invariant): packed row coordinates
+    // (bit 31: the upper four channels are past the last, bits 29, 30: the ci
+    // or co tile) and byte offset from the brick's first voxel (kNone: no such
+    // channels). x unit: channels 8 q.. of slot
+    // r of ci tile j; dy unit: channels 8 q.. of brick voxel f of co tile c.
+    uint32_t xpk[C::XU], xrel[C::XU], dpk[C::DU], drel[C::DU];
+    const int nxu = a.nci * a.nxs * 4, ndu = WCO * a.V * 4;
+#pragma unroll
+    for (int i = 0; i < C::XU; ++i) {
+        const int s = tid + i * kThreadsA;
+        xpk[i] = 0;
+        xrel[i] = kNone;
+        if (s < nxu) {
+            const int q = s & 3, r = s >> 2;
+            const int j = (r >= a.nxs) + (r >= 2 * a.nxs) + (r >= 3 * a.nxs);
+            const uint32_t pk = xtab[r - j * a.nxs];
+            const int z = int(pk >> 20), y = int((pk >> 10) & 1023), x = int(pk & 1023);
+            const int c = ci0 + j * 32 + 8 * q;
+            xpk[i] = pk | (uint32_t(j) << 29) |
+                     (R == 2 && c + 4 >= a.cin ? 0x80000000u : 0u);
+            if (c < a.cin) xrel[i] = uint32_t(z) * a.xplane + uint32_t(y) * a.xrow + uint32_t(x * a.cin + c) * ESZ;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < C::DU; ++i) {
+        const int s = tid + i * kThreadsA;
+        dpk[i] = 0;
+        drel[i] = kNone;
+        if (s < ndu) {
+            const int q = s & 3, r = s >> 2;
+            const int ct = r >> a.lv, f = r & (a.V - 1);
+            const int x = f & (a.BO[2] - 1), y = (f >> a.lb2) & (a.BO[1] - 1), z = f >> (a.lb1 + a.lb2);
+            const int c = co0 + ct * 32 + 8 * q;
+            dpk[i] = (uint32_t(z) << 20) | (uint32_t(y) << 10) | uint32_t(x) | (uint32_t(ct) << 29) |
+                     (R == 2 && c + 4 >= a.cout ? 0x80000000u : 0u);
+            if (c < a.cout) drel[i] = uint32_t(z) * a.yplane + uint32_t(y) * a.yrow + uint32_t(x * a.cout + c) * ESZ;
+        }
+    }
+    // Geometry of a brick: the first voxel its taps meet, and per axis the rows
+    // [lo, hi) relative to it that are read (in the tile and met by an output)
+    struct Geo {
+        int64_t nn;
+        int ob[3], i0[3], lo[3], hi[3];
+        bool inside, dfull, margin;
+    };
+    // the position of the brick that is staged next, advanced brick by brick
+    struct Pos {
+        int bx, by, bz, nn;
+    } sp;
+    {
+        uint32_t b = uint32_t(br0);
+        sp.bx = int(b % uint32_t(a.NB[2]));
+        b /= uint32_t(a.NB[2]);
+        sp.by = int(b % uint32_t(a.NB[1]));
+        b /= uint32_t(a.NB[1]);
+        sp.bz = int(b % uint32_t(a.NB[0]));
+        sp.nn = int(b / uint32_t(a.NB[0]));
+    }
+    auto advance = [&]() SC_INLINE {
+        if (++sp.bx < a.NB[2]) return;
+        sp.bx = 0;
+        if (++sp.by < a.NB[1]) return;
+        sp.by = 0;
+        if (++sp.bz < a.NB[0]) return;
+        sp.bz = 0;
+        ++sp.nn;
+    };
+    auto geometry = [&]() SC_INLINE {
+        Geo g;
+        g.nn = sp.nn;
+        g.ob[0] = sp.bz * a.BO[0], g.ob[1] = sp.by * a.BO[1], g.ob[2] = sp.bx * a.BO[2];
+        g.inside = g.dfull = true;
+        g.margin = false;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            g.i0[k] = g.ob[k] * a.S[k] + k0[k] - a.pad[k];
+            const int ext = (a.BO[k] - 1) * a.S[k] + a.KG[k];
+            const int used = (min(a.BO[k], a.O[k] - g.ob[k]) - 1) * a.S[k] + a.KG[k];
+            g.lo[k] = max(0, -g.i0[k]);
+            g.hi[k] = min(used, a.P[k] - g.i0[k]);
+            g.inside = g.inside && g.lo[k] == 0 && g.hi[k] == ext;
+            g.dfull = g.dfull && g.ob[k] + a.BO[k] <= a.O[k];
+            if (SLOW && ((a.fold.mask >> k) & 1u))
+                g.margin = g.margin || (g.lo[k] < g.hi[k] && (g.i0[k] + g.lo[k] < int(a.fold.lo[k]) ||
+                                                              g.i0[k] + g.hi[k] > int(a.fold.lo[k] + a.fold.ext[k])));
+        }
+        return g;
+    };
+    auto x_in = [&](const Geo& g, int z, int y, int x) SC_INLINE {
+        return z >= g.lo[0] && z < g.hi[0] && y >= g.lo[1] && y < g.hi[1] && x >= g.lo[2] && x < g.hi[2];
+    };
+    auto d_in = [&](const Geo& g, int z, int y, int x) SC_INLINE {
+        return g.ob[0] + z < a.O[0] && g.ob[1] + y < a.O[1] && g.ob[2] + x < a.O[2];
+    };
+
+    // The fast path: whole 16-byte vectors of the tile and dy through buffer
+    // loads (an offset of kNone loads zeros). bf16: straight into LDS, where unit
+    // s of the input lies at 16 s and of dy at dy_off + 16 s; binary32: into
+    // registers until the brick's turn to be split and written.
+    struct Unit {
+        uint4 v[R];
+    };
+    Unit xv[C::XU], dv[C::DU];
+    auto fetch = [&](__amdgpu_buffer_rsrc_t r, uint32_t off, bool half, char* dst, Unit& u) SC_INLINE {
+        if constexpr (DMA) {
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(r, SC_LDSY(dst), 16, off, 0, 0, 0);
+        } else {
+            const auto v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+            const auto w = __builtin_amdgcn_raw_buffer_load_b128(r, half ? kNone : off + 16, 0, 0);
+            u.v[0] = make_uint4(v[0], v[1], v[2], v[3]);
+            u.v[R - 1] = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+    };
+    auto issue = [&](const Geo& g, int buf) SC_INLINE {
+        const int64_t xorg = g.nn * a.xbatch + int64_t(g.i0[0]) * a.xplane + int64_t(g.i0[1]) * a.xrow +
+                             int64_t(g.i0[2]) * (a.cin * ESZ);
+        const int64_t yorg = g.nn * a.ybatch + int64_t(g.ob[0]) * a.yplane + int64_t(g.ob[1]) * a.yrow +
+                             int64_t(g.ob[2]) * (a.cout * ESZ);
+        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(a.tile) + xorg, short(0),
+                                                                            0x7FFFFFF0, 0x00020000);
+        const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(a.dy) + yorg, short(0),
+                                                                            0x7FFFFFF0, 0x00020000);
+        char* st = lds + buf * a.stageb + wave * 1024;
+#pragma unroll
+        for (int i = 0; i < C::XU; ++i) {
+            if (i * kThreadsA >= nxu) continue;
+            const uint32_t pk = xpk[i];
+            const int z = int((pk >> 20) & 511), y = int((pk >> 10) & 1023), x = int(pk & 1023);
+            bool ok = xrel[i] != kNone && (g.inside || x_in(g, z, y, x));
+            if constexpr (SLOW && DMA) {
+                // a brick that touches a folded margin: lanes whose voxel lies in a
+                // slab load it from there, the others below (the tile, or zeros)
+                if (g.margin && ok) {
+                    const char* v = fold_voxel(a.fold, a.tile, g.nn, g.i0[0] + z, g.i0[1] + y, g.i0[2] + x, a.cin * ESZ);
+                    const char* t = a.tile + xorg + xrel[i];
+                    const int c = ci0 + int((pk >> 29) & 3) * 32 + 8 * (tid & 3);
+                    if (!v) {
+                        ok = false;
+                    } else if (v + c * ESZ != t) {
+                        __builtin_amdgcn_global_load_lds(v + c * ESZ, SC_LDSY(st + i * (kThreadsA * 16)), 16, 0, 0);
+                        continue;
+                    }
+                }
+            }
+            fetch(rx, ok ? xrel[i] : kNone, !ok || (pk >> 31), st + i * (kThreadsA * 16), xv[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < C::DU; ++i) {
+            if (i * kThreadsA >= ndu) continue;
+            const uint32_t pk = dpk[i];
+            const bool ok = drel[i] != kNone && (g.dfull || d_in(g, int((pk >> 20) & 511), int((pk >> 10) & 1023),
+                                                            int(pk & 1023)));
+            fetch(ry, ok ? drel[i] : kNone, !ok || (pk >> 31), st + a.dy_off + i * (kThreadsA * 16), dv[i]);
+        }
+    };
+    auto put = [&](char* dst, int pstride, const Unit& u) SC_INLINE {
+        if constexpr (PARTS == 1) {
+            *reinterpret_cast<uint4*>(dst) = u.v[0];
+        } else {
+            float v[8];
+            __builtin_memcpy(v, &u, sizeof(v));
+            uint4 h, m, l;
+            split_bf16x3(v, h, m, l);
+            *reinterpret_cast<uint4*>(dst) = h;
+            *reinterpret_cast<uint4*>(dst + pstride) = m;
+            *reinterpret_cast<uint4*>(dst + 2 * pstride) = l;
+        }
+    };
+    // split and write the units that issue loaded
+    auto commit = [&](int buf) SC_INLINE {
+        char* st = lds + buf * a.stageb + tid * 16;
+#pragma unroll
+        for (int i = 0; i < C::XU; ++i)
+            if (tid + i * kThreadsA < nxu)
+                put(st + i * (kThreadsA * 16) + int((xpk[i] >> 29) & 3) * (PARTS - 1) * xps, xps, xv[i]);
+#pragma unroll
+        for (int i = 0; i < C::DU; ++i)
+            if (tid + i * kThreadsA < ndu)
+                put(st + a.dy_off + i * (kThreadsA * 16) + int((dpk[i] >> 29) & 3) * (PARTS - 1) * (a.V * 64),
+                    a.V * 64, dv[i]);
+    };
+    // stage a brick unit by unit: each voxel from its own buffer (a folded
+    // margin), channels one by one where they are not whole aligned vectors
+    auto stage_slow = [&](const Geo& g, int buf) SC_INLINE {
+        char* st = lds + buf * a.stageb;
+        auto load = [&](const char* vox, int c, int cend, bool whole) SC_INLINE {
+            Unit u;
+#pragma unroll
+            for (int r = 0; r < R; ++r) u.v[r] = make_uint4(0, 0, 0, 0);
+            if (vox && c < cend) {
+                const T* p = reinterpret_cast<const T*>(vox) + c;
+                if (whole) {
+                    u.v[0] = *reinterpret_cast<const uint4*>(p);
+                    if (R == 2 && c + 4 < cend) u.v[R - 1] = *reinterpret_cast<const uint4*>(p + 4);
+                } else {
+                    T e[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) e[k] = c + k < cend ? p[k] : T(0);
+                    __builtin_memcpy(&u, e, sizeof(e));
+                }
+            }
+            return u;
+        };
+#pragma unroll 1
+        for (int s0 = tid; s0 < nxu; s0 += C::SU * kThreadsA) {
+            // SU units' loads in flight before their writes
+            Unit u[C::SU];
+            int dst[C::SU];
+#pragma unroll
+            for (int k = 0; k < C::SU; ++k) {
+                const int s = s0 + k * kThreadsA;
+                dst[k] = -1;
+                if (s < nxu) {
+                    const int r = s >> 2, j = (r >= a.nxs) + (r >= 2 * a.nxs) + (r >= 3 * a.nxs);
+                    const uint32_t pk = lds_read_u32(lds0 + uint32_t(a.xtab_off + (r - j * a.nxs) * 4));
+                    const int z = int(pk >> 20), y = int((pk >> 10) & 1023), x = int(pk & 1023);
+                    const char* vox = nullptr;
+                    if (x_in(g, z, y, x))
+                        vox = fold_voxel(a.fold, a.tile, g.nn, g.i0[0] + z, g.i0[1] + y, g.i0[2] + x,
+                                         int64_t(a.cin) * ESZ);
+                    u[k] = load(vox, ci0 + j * 32 + 8 * (s & 3), a.cin, a.xvec != 0);
+                    dst[k] = s * 16 + j * (PARTS - 1) * xps;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < C::SU; ++k)
+                if (dst[k] >= 0) put(st + dst[k], xps, u[k]);
+        }
+#pragma unroll 1
+        for (int s = tid; s < ndu; s += kThreadsA) {
+            const int r = s >> 2, ct = r >> a.lv, f = r & (a.V - 1);
+            const int x = f & (a.BO[2] - 1), y = (f >> a.lb2) & (a.BO[1] - 1), z = f >> (a.lb1 + a.lb2);
+            const char* vox = nullptr;
+            if (d_in(g, z, y, x))
+                vox = a.dy + g.nn * a.ybatch + int64_t(g.ob[0] + z) * a.yplane + int64_t(g.ob[1] + y) * a.yrow +
+                      int64_t(g.ob[2] + x) * (a.cout * ESZ);
+            put(st + a.dy_off + s * 16 + ct * (PARTS - 1) * (a.V * 64), a.V * 64,
+                load(vox, co0 + ct * 32 + 8 * (s & 3), a.cout, a.dvec != 0));
+        }
+    };
+
+    f32x16_y acc[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[u][e] = 0.f;
+
+    const int vl = 8 * (lane >> 5) + ((lane & 15) >> 2);                   // the lane's voxel of a K step
+    const uint32_t colb = (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;  // its channels, bytes
+    // Offset of brick voxel f in the staged input. The brick's extents are powers
+    // of two, so its coordinates are bit fields of f and the offset of 16 ks + l
+    // (l < 16) is the sum of the two offsets: the lane's part is formed once, the
+    // K step's is uniform. The W extent is at least 8: voxel f + 4 lies in the
+    // same row, 256 bytes further.
+    auto voff = [&](int f) SC_INLINE {
+        const int x = f & (a.BO[2] - 1), y = (f >> a.lb2) & (a.BO[1] - 1), z = f >> (a.lb1 + a.lb2);
+        return uint32_t(((z * a.NS[1] + y) * a.NS[2] + x) * 64);
+    };
+    const uint32_t lane0 = voff(vl);
+    struct Frag {
+        uint2 p[PARTS][2];
+    };
+    auto ready = [&](Frag& f) SC_INLINE {
+#pragma unroll
+        for (int p = 0; p < PARTS; ++p) {
+            lds_ready(f.p[p][0]);
+            lds_ready(f.p[p][1]);
+        }
+    };
+    auto op = [&](const uint2 (&v)[2]) SC_INLINE {
+        return __builtin_bit_cast(bf16x8_y, make_uint4(v[0].x, v[0].y, v[1].x, v[1].y));
+    };
+    // wait until at most n (a constant after unrolling) LDS operations are outstanding
+    auto lds_wait_n = [&](int n) SC_INLINE {
+        switch (n) {
+        case 0: lds_wait<0>(); break;
+        case 2: lds_wait<2>(); break;
+        case 4: lds_wait<4>(); break;
+        case 6: lds_wait<6>(); break;
+        case 8: lds_wait<8>(); break;
+        case 10: lds_wait<10>(); break;
+        case 12: lds_wait<12>(); break;
+        default: lds_wait<14>(); break;
+        }
+    };
+    // K steps ks0, ks0 + KS, ... of the brick in buffer `buf`. The operands of
+    // the next units are read while unit u multiplies (LDS operations complete in
+    // order, two per 16-voxel operand).
+    auto compute = [&](int buf, int br) SC_INLINE {
+        const uint32_t xs = lds0 + uint32_t(buf * a.stageb) + colb;
+        const uint32_t ds = xs + uint32_t(a.dy_off + wco * PARTS * a.V * 64);
+        const int nks = a.V >> 4;
+        if constexpr (PARTS == 1 && !SLOW) {
+            // Every operand is read a whole K step ahead (an LDS read takes far
+            // longer than one MFMA): once unit u's product is issued, its registers
+            // take unit u of the next K step. The counter of outstanding LDS
+            // operations holds 15, so at most seven units are waited past.
+            if (ks0 >= nks) return;
+            auto afrag = [&](int ks, uint2 (&f)[2]) SC_INLINE {
+                const uint32_t ad = ds + uint32_t(16 * ks + vl) * 64;
+                f[0] = lds_read_tr16_b64(ad);
+                f[1] = lds_read_tr16_b64<256>(ad);
+            };
+            auto bfrag = [&](uint32_t v0, int u, uint2 (&f)[2]) SC_INLINE {
+                const uint32_t ad = v0 + uint32_t(toff[u]);
+                f[0] = lds_read_tr16_b64(ad);
+                f[1] = lds_read_tr16_b64<256>(ad);
+            };
+            uint2 af[2], an[2], bv[NU][2];
+            {
+                const uint32_t v0 = lane0 + xs + voff(16 * ks0);
+                afrag(ks0, af);
+#pragma unroll
+                for (int u = 0; u < NU; ++u) bfrag(v0, u, bv[u]);
+            }
+            // A: its two reads come before the units' of its K step
+            lds_wait_n(2 * NU);
+            lds_ready(af[0]);
+            lds_ready(af[1]);
+            auto product = [&](int u) SC_INLINE {
+                lds_ready(bv[u][0]);
+                lds_ready(bv[u][1]);
+                acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op(af), op(bv[u]), acc[u], 0, 0, 0);
+            };
+            int ks = ks0;
+            for (; ks + KS < nks; ks += KS) {
+                const uint32_t v0 = lane0 + xs + voff(16 * (ks + KS));
+                afrag(ks + KS, an);
+#pragma unroll
+                for (int u = 0; u < NU; ++u) {
+                    // issued after unit u's reads: those of the other NU - 1 units
+                    // (of this step or the next) and the next A
+                    lds_wait_n(2 * NU);
+                    product(u);
+                    bfrag(v0, u, bv[u]);
+                }
+                lds_wait_n(2 * NU);
+                lds_ready(an[0]);
+                lds_ready(an[1]);
+                af[0] = an[0];
+                af[1] = an[1];
+            }
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                lds_wait_n(2 * (NU - 1 - u));
+                product(u);
+            }
+            return;
+        }
+        for (int ks = ks0; ks < nks; ks += KS) {
+            const uint32_t f = uint32_t(16 * ks + vl);
+            Frag av;
+#pragma unroll
+            for (int p = 0; p < PARTS; ++p) {
+                const uint32_t ad = ds + uint32_t(p * a.V * 64) + f * 64;
+                av.p[p][0] = lds_read_tr16_b64(ad);
+                av.p[p][1] = lds_read_tr16_b64<256>(ad);
+            }
+            const uint32_t v0 = lane0 + xs + voff(16 * ks);
+            auto loadb = [&](int u, int p, uint2 (&b)[2]) SC_INLINE {
+                const uint32_t ad = v0 + uint32_t(toff[u] + p * xps);
+                b[0] = lds_read_tr16_b64(ad);
+                b[1] = lds_read_tr16_b64<256>(ad);
+            };
+            if constexpr (PARTS == 1) {
+                // PRE units are read ahead within the K step (the registers of the
+                // SLOW variants hold no more)
+                constexpr int PRE = NU < 4 ? NU - 1 : 3, RB = PRE + 1;
+                uint2 bv[RB][2];
+#pragma unroll
+                for (int u = 0; u < PRE; ++u) loadb(u, 0, bv[u]);
+#pragma unroll
+                for (int u = 0; u < NU; ++u) {
+                    if (u + PRE < NU) loadb(u + PRE, 0, bv[(u + PRE) % RB]);
+                    lds_wait_n(2 * (NU - 1 - u < PRE ? NU - 1 - u : PRE));
+                    if (u == 0) ready(av);
+                    lds_ready(bv[u % RB][0]);
+                    lds_ready(bv[u % RB][1]);
+                    acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op(av.p[0]), op(bv[u % RB]), acc[u], 0, 0, 0);
+                }
+            } else {
+                // The six products of a K step are summed from zero and then added
+                // to the accumulator: the MFMA aligns its products to its addend
+                // with fewer bits than binary32 has, which over thousands of K
+                // steps costs more than the one rounding of this add. What the MFMA
+                // cuts off has a mean (it cuts towards minus infinity, about 3e-8 of
+                // a product per K step), so every other K step is computed with dy
+                // negated and subtracted: the means cancel. Weight gradient of 8 x 8
+                // channels over 2 M voxels, relative error: 2.5e-6 without, 1.1e-6
+                // with v_mfma_f32_32x32x2_f32.
+                // A part of the input is read for the next unit as soon as this
+                // unit's last product with it is under way.
+                const bool neg = ((br + ks0 + ks / KS) & 1) != 0;
+                const uint32_t flip = neg ? 0x80008000u : 0u;
+                const float sgn = neg ? -1.f : 1.f;
+                uint2 bv[3][2];
+#pragma unroll
+                for (int p = 2; p >= 0; --p) loadb(0, p, bv[p]);
+#pragma unroll
+                for (int u = 0; u < NU; ++u) {
+                    f32x16_y t = {};
+                    auto part = [&](auto p_c) SC_INLINE {
+                        constexpr int p = decltype(p_c)::value;
+                        // issued after this part's two reads: those of the two parts
+                        // that follow it (of this unit or the next)
+                        if (u + 1 < NU)
+                            lds_wait<4>();
+                        else
+                            lds_wait<2 * p>();
+                        if (u == 0 && p == 2) {
+                            ready(av);
+#pragma unroll
+                            for (int i = 0; i < PARTS; ++i)
+#pragma unroll
+                                for (int h = 0; h < 2; ++h)
+                                    av.p[i][h] = make_uint2(av.p[i][h].x ^ flip, av.p[i][h].y ^ flip);
+                        }
+                        lds_ready(bv[p][0]);
+                        lds_ready(bv[p][1]);
+#pragma unroll
+                        for (int i = 2 - p; i >= 0; --i)
+                            t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op(av.p[i < PARTS ? i : 0]), op(bv[p]), t, 0, 0,
+                                                                         0);
+                        if (u + 1 < NU) loadb(u + 1, p, bv[p]);
+                    };
+                    part(std::integral_constant<int, 2>{});
+                    part(std::integral_constant<int, 1>{});
+                    part(std::integral_constant<int, 0>{});
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[u][e] = fmaf(t[e], sgn, acc[u][e]);
+                }
+            }
+        }
+    };
+
+    if constexpr (DMA) {
+        // ring of nbuf buffers: iteration br waits for its own brick's loads (the
+        // loads of the nbuf - 2 bricks after it stay in flight), then fills the
+        // buffer that the previous iteration multiplied with brick br + nbuf - 1:
+        // waves 0-3 before they multiply, waves 4-7 after, so that a SIMD's two
+        // waves overlap the bookkeeping of one with the products of the other.
+        const int nbuf = a.nbuf;
+        const int per = (nxu + kThreadsA - 1) / kThreadsA + (ndu + kThreadsA - 1) / kThreadsA;
+        const bool vec = !SLOW || (a.xvec && a.dvec);
+        int bi = 0, bo = 0;
+        for (int br = br0 - (nbuf - 1); br < br1; ++br) {
+            if (br >= br0) {
+                wait_vm_dyn(nbuf == 3 && br + 1 < br1 && vec ? per : 0);
+                wait_barrier();
+            }
+#pragma unroll 1
+            for (int h = 0; h < 2; ++h) {
+                if ((h == 0) == (wave < 4)) {
+                    if (br + nbuf - 1 < br1) {
+                        const Geo g = geometry();
+                        advance();
+                        if (SLOW && !vec)
+                            stage_slow(g, bi);
+                        else
+                            issue(g, bi);
+                    }
+                } else if (br >= br0) {
+                    compute(bo, br);
+                }
+            }
+            bi = bi + 1 == nbuf ? 0 : bi + 1;
+            if (br >= br0) bo = bo + 1 == nbuf ? 0 : bo + 1;
+        }
+        lds_wait<0>();
+        __syncthreads();
+    } else {
+        // Iteration br fills the buffer of brick br + 1 and multiplies brick br
+        // (it also loads brick br + 2). The buffer filled was last read before the
+        // barrier that ended the previous iteration, so it may be filled at any
+        // time in this one.
+        for (int br = br0 - 2; br < br1; ++br) {
+#pragma unroll 1
+            for (int h = 0; h < 2; ++h) {
+                if ((h == 0) == (wave < 4)) {
+                    const int b1 = br + 1, b2 = br + 2, buf = (b1 - br0) & 1;
+                    if (b1 >= br0 && b1 < br1) {
+                        if constexpr (SLOW) {
+                            stage_slow(geometry(), buf);
+                            advance();
+                        } else {
+                            commit(buf);
+                        }
+                    }
+                    if constexpr (!SLOW) {
+                        if (b2 < br1) {
+                            issue(geometry(), 0);
+                            advance();
+                        }
+                    }
+                } else if (br >= br0) {
+                    compute((br - br0) & 1, br);
+                }
+            }
+            __syncthreads();
+        }
+    }
+
+    // partial [co tile][unit][r4][lane][4]: element 4 r4 + e of a tile is row
+    // 8 r4 + 4 (lane / 32) + e, column lane % 32
+    float4* out = reinterpret_cast<float4*>(a.part) +
+                  (((int64_t(split) * a.nmb + mb) * a.ncb + cb) * a.ntg + tg) * (WCO * WU * NU * 256);
+    auto quad = [&](int u, int r4) SC_INLINE {
+        return make_float4(acc[u][4 * r4], acc[u][4 * r4 + 1], acc[u][4 * r4 + 2], acc[u][4 * r4 + 3]);
+    };
+    if constexpr (KS == 1) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) out[((wco * WU + wu) * NU + u) * 256 + r4 * 64 + lane] = quad(u, r4);
+    } else {
+        // the K-split waves' accumulators are added through LDS, in wave order,
+        // kRedUnits units at a time
+        float4* red = reinterpret_cast<float4*>(lds);
+        constexpr int W1 = WCO * WU, RU = kRedUnits;
+#pragma unroll
+        for (int u0 = 0; u0 < NU; u0 += RU) {
+            if (u0 > 0) __syncthreads();
+#pragma unroll
+            for (int d = 0; d < RU; ++d)
+                if (u0 + d < NU)
+#pragma unroll
+                    for (int r4 = 0; r4 < 4; ++r4)
+                        red[(((ks0 * WCO + wco) * WU + wu) * RU + d) * 256 + r4 * 64 + lane] = quad(u0 + d, r4);
+            __syncthreads();
+            for (int e = tid; e < W1 * RU * 256; e += kThreadsA) {
+                const int w = e / (RU * 256), d = (e / 256) % RU, x = e & 255;
+                if (u0 + d >= NU) continue;
+                float4 s = red[e];
+#pragma unroll
+                for (int k = 1; k < KS; ++k) {
+                    const float4 t = red[k * W1 * RU * 256 + e];
+                    s.x += t.x;
+                    s.y += t.y;
+                    s.z += t.z;
+                    s.w += t.w;
+                }
+                out[(w * NU + u0 + d) * 256 + x] = s;
+            }
+        }
+    }
+}
+
+struct AnyRed {
+    const float* part;
+    float* dw;
+    uint32_t* status;
+    int32_t nsplit, nmb, ncb, ntg, wco, nu, tpg, nci, cin, cout;
+    int32_t KG[3], NG[3], K[3];
+    int64_t total;  // floats of all groups' partials of one split
+};
+
+// Sum the partials over the splits in a fixed order and scatter into
+// dw[co][ci][tap]; clears the call's status word. A block owns 64 consecutive
+// partial floats; each of its four waves sums a quarter of the splits (reads are
+// coalesced, eight in flight) and the quarters are added in order: with up to 256
+// splits and as few as 9216 floats one thread per float took 13 us, this 6.
+__global__ __launch_bounds__(256) void wgrad_any_reduce(AnyRed a)
+{
+    __shared__ float quarter[4][64];
+    const int lane64 = threadIdx.x & 63, w4 = threadIdx.x >> 6;
+    const int64_t e = int64_t(blockIdx.x) * 64 + lane64;  // the total is a multiple of 64
+    if (e == 0 && w4 == 0) a.status[0] = 0u;
+    {
+        const int sp0 = a.nsplit * w4 / 4, sp1 = a.nsplit * (w4 + 1) / 4;
+        float s8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        const float* src = a.part + e;
+        int sp = sp0;
+        for (; sp + 8 <= sp1; sp += 8) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) s8[k] += src[(sp + k) * a.total];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (sp + k < sp1) s8[k] += src[(sp + k) * a.total];
+        quarter[w4][lane64] = ((s8[0] + s8[1]) + (s8[2] + s8[3])) + ((s8[4] + s8[5]) + (s8[6] + s8[7]));
+    }
+    __syncthreads();
+    if (w4 != 0) return;
+    const float s = (quarter[0][lane64] + quarter[1][lane64]) + (quarter[2][lane64] + quarter[3][lane64]);
+    const uint32_t blk = uint32_t(a.wco) * a.nu * 1024u;
+    const uint32_t grp = uint32_t(e / blk), p = uint32_t(e - int64_t(grp) * blk);
+    const int tg = int(grp % uint32_t(a.ntg)), cb = int(grp / uint32_t(a.ntg)) % a.ncb,
+              mb = int(grp / (uint32_t(a.ntg) * a.ncb));
+    const int q = p & 3, lane = (p >> 2) & 63, r4 = (p >> 8) & 3, wu = p >> 10;
+    const int u = wu % a.nu, w = wu / a.nu;
+    const int j = u / a.tpg, t = u - j * a.tpg;
+    const int g2 = tg % a.NG[2], g1 = (tg / a.NG[2]) % a.NG[1], g0 = tg / (a.NG[2] * a.NG[1]);
+    const int t2 = g2 * a.KG[2] + t % a.KG[2], t1 = g1 * a.KG[1] + (t / a.KG[2]) % a.KG[1],
+              t0 = g0 * a.KG[0] + t / (a.KG[2] * a.KG[1]);
+    const int co = (mb * a.wco + w) * 32 + 8 * r4 + 4 * (lane >> 5) + q;
+    const int ci = (cb * a.nci + j) * 32 + (lane & 31);
+    if (j >= a.nci || co >= a.cout || ci >= a.cin || t0 >= a.K[0] || t1 >= a.K[1] || t2 >= a.K[2]) return;
+    a.dw[((int64_t(co) * a.cin + ci) * a.K[0] + t0) * a.K[1] * a.K[2] + t1 * a.K[2] + t2] = s;
+}
+
+struct AnyPlan {
+    bool ok;
+    int wco, wu, nu;
+    AnyArgs a;
+    size_t lds, part_bytes;
+};
+
+constexpr size_t kLdsAny = 160 * 1024;
+
+AnyPlan plan_any(const Tile3& t, const Conv3& cv, shard_dtype_t dt)
+{
+    AnyPlan pl{};
+    pl.ok = false;
+    if (force_generic()) return pl;
+    const bool f32 = dt == SHARD_F32;
+    const int parts = f32 ? 3 : 1, esz = f32 ? 4 : 2;
+    for (int k = 0; k < 3; ++k)
+        if (cv.K[k] > 64 || cv.S[k] > 64 || cv.O[k] > (int64_t(1) << 24) || t.P[k] > (int64_t(1) << 28) ||
+            std::abs(cv.pad[k]) > (1 << 28))
+            return pl;
+    if (t.c > 4096 || cv.cout > 4096 || t.n * cv.out_voxels() == 0) return pl;
+    AnyArgs& a = pl.a;
+    a.cin = int32_t(t.c);
+    a.cout = int32_t(cv.cout);
+    for (int k = 0; k < 3; ++k) {
+        a.P[k] = int32_t(t.P[k]);
+        a.O[k] = int32_t(cv.O[k]);
+        a.S[k] = int32_t(cv.S[k]);
+        a.pad[k] = int32_t(cv.pad[k]);
+    }
+    // taps per group: whole W rows of taps where they fit, then rows of one
+    // plane, then planes, at most nine in all
+    int room = kMaxTaps;
+    for (int k = 2; k >= 0; --k) {
+        const int K = int(cv.K[k]);
+        a.KG[k] = std::min(K, room);
+        a.NG[k] = (K + a.KG[k] - 1) / a.KG[k];
+        a.KG[k] = (K + a.NG[k] - 1) / a.NG[k];  // even groups
+        room = a.NG[k] > 1 ? 1 : room / a.KG[k];
+    }
+    a.tpg = a.KG[0] * a.KG[1] * a.KG[2];
+    a.ntg = a.NG[0] * a.NG[1] * a.NG[2];
+    const int ntco = int(ceil_div(cv.cout, 32)), ntci = int(ceil_div(t.c, 32));
+    // ci tiles per workgroup while the units fit one wave; output channels in
+    // one workgroup (up to 128) so that the input is staged once for them
+    a.nci = std::max(1, std::min(std::min(ntci, 4), kMaxTaps / a.tpg));
+    pl.wco = ntco >= 3 ? 4 : ntco;
+    a.nmb = (ntco + pl.wco - 1) / pl.wco;
+    a.ncb = (ntci + a.nci - 1) / a.nci;
+    const int units = a.nci * a.tpg;
+
+    const int64_t vb = t.c * esz, yb = cv.cout * esz;
+    const int64_t xrow = t.P[2] * vb, xplane = t.P[1] * xrow, yrow = cv.O[2] * yb, yplane = cv.O[1] * yrow;
+    const int64_t xstr[3] = {xplane, xrow, vb}, ystr[3] = {yplane, yrow, yb};
+    // per axis and power of two b: staged rows, share of the outputs' bricks that
+    // is in range, whether the packed coordinates hold the footprint, and the
+    // bytes it spans (offsets within it are 32-bit)
+    const int64_t lim = (int64_t(1) << 31) - 64;
+    int64_t xspan[3][7], yspan[3][7];
+    constexpr int kB = 7;  // brick extents 1 .. 64
+    int64_t cnt[3][kB];
+    double eff[3][kB];
+    bool ok[3][kB];
+    for (int k = 0; k < 3; ++k)
+        for (int i = 0; i < kB; ++i) {
+            const int b = 1 << i;
+            cnt[k][i] = slot_count(b, a.KG[k], a.S[k]);
+            eff[k][i] = double(cv.O[k]) / double(ceil_div(cv.O[k], b) * b);
+            const int64_t rows = int64_t(b - 1) * a.S[k] + a.KG[k];
+            ok[k][i] = rows <= (k == 0 ? 512 : 1024);
+            xspan[k][i] = rows * xstr[k];
+            yspan[k][i] = b * ystr[k];
+        }
+    double best = 1e300;
+    // two unit halves (WU = 2) only for narrow outputs, where eight K-split waves
+    // ask for bricks whose strided footprint does not fit
+    for (int wu = 1; wu <= (pl.wco == 1 && units > 1 ? 2 : 1); ++wu) {
+        const int per = (units + wu - 1) / wu;
+        const int nu = per <= 1 ? 1 : per <= 5 ? 5 : per <= 7 ? 7 : 9;
+        const int ks = 8 / (pl.wco * wu);
+        const int XU = !f32 ? AnyT<bf16_t, 1>::XU : nu <= 5 ? AnyT<float, 5>::XU : AnyT<float, 9>::XU;
+        const int DU = !f32 ? AnyT<bf16_t, 1>::DU : nu <= 5 ? AnyT<float, 5>::DU : AnyT<float, 9>::DU;
+        for (int lv = 4; lv <= 10; ++lv) {
+            const int V = 1 << lv;
+            if (pl.wco * V * 4 > DU * kThreadsA) break;
+            for (int l2 = 3; l2 < kB && l2 <= lv; ++l2) {
+                for (int l1 = 0; l1 < kB && l1 + l2 <= lv; ++l1) {
+                    const int l0 = lv - l1 - l2;
+                    if (l0 >= kB || !ok[0][l0] || !ok[1][l1] || !ok[2][l2]) continue;
+                    const int64_t nxs = cnt[0][l0] * cnt[1][l1] * cnt[2][l2];
+                    if (a.nci * nxs * 4 > XU * kThreadsA ||
+                        xspan[0][l0] + xspan[1][l1] + xspan[2][l2] >= lim ||
+                        yspan[0][l0] + yspan[1][l1] + yspan[2][l2] >= lim)
+                        continue;
+                    // direct loads write whole 8 KiB rounds of the workgroup
+                    const int64_t xb = f32 ? a.nci * nxs * 192 : round_up(a.nci * nxs * 64, kThreadsA * 16);
+                    const int64_t db =
+                        f32 ? int64_t(pl.wco) * V * 192 : round_up(int64_t(pl.wco) * V * 64, kThreadsA * 16);
+                    const int64_t stage = xb + db, tabs = nxs * 4;
+                    const int nbuf = !f32 && 3 * stage + tabs <= int64_t(kLdsAny) ? 3 : 2;
+                    const size_t lds = std::max<size_t>(size_t(nbuf * stage + tabs), size_t(8 * kRedUnits * 4096));
+                    if (lds > kLdsAny) continue;
+                    // cycles of a SIMD per brick: MFMAs (two waves) or transposed
+                    // reads, then staging; waves without a K step idle
+                    const int steps = (V / 16 + ks - 1) / ks;
+                    const double mfma = 2.0 * steps * nu * (f32 ? 192.0 : 32.0);
+                    const double reads = 8.0 * steps * (2 + 2 * nu) * parts * 2.9;
+                    const double bytes = double(a.nci * nxs + pl.wco * V) * 32 * esz;
+                    const double cost = (std::max(std::max(mfma, reads), bytes / 12.0) + 0.02 * bytes +
+                                         (f32 || nbuf == 3 ? 400.0 : 1200.0)) /
+                                        (double(V) * eff[0][l0] * eff[1][l1] * eff[2][l2]);
+                    if (cost < best) {
+                        best = cost;
+                        pl.wu = wu;
+                        pl.nu = nu;
+                        pl.lds = lds;
+                        a.V = V;
+                        a.lv = lv;
+                        a.lb1 = l1;
+                        a.lb2 = l2;
+                        const int l[3] = {l0, l1, l2};
+                        for (int k = 0; k < 3; ++k) {
+                            a.BO[k] = 1 << l[k];
+                            a.NS[k] = int32_t(cnt[k][l[k]]);
+                            a.NB[k] = int32_t(ceil_div(cv.O[k], a.BO[k]));
+                        }
+                        a.nxs = int32_t(nxs);
+                        a.stageb = int32_t(stage);
+                        a.dy_off = int32_t(xb);
+                        a.nbuf = nbuf;
+                    }
+                }
+            }
+        }
+    }
+    if (best >= 1e299) return pl;
+    a.xtab_off = a.nbuf * a.stageb;
+    for (int u = 0; u < 2 * kMaxTaps; ++u) {
+        const int uu = u < units ? u : 0;  // idle units repeat unit 0
+        const int j = uu / a.tpg, tp = uu - j * a.tpg;
+        const int t2 = tp % a.KG[2], t1 = (tp / a.KG[2]) % a.KG[1], t0 = tp / (a.KG[2] * a.KG[1]);
+        const int slot = (slot_of_tap(a.BO[0], a.KG[0], a.S[0], t0) * a.NS[1] +
+                          slot_of_tap(a.BO[1], a.KG[1], a.S[1], t1)) * a.NS[2] +
+                         slot_of_tap(a.BO[2], a.KG[2], a.S[2], t2);
+        a.utoff[u] = j * parts * a.nxs * 64 + slot * 64;
+    }
+    a.xrow = uint32_t(xrow);
+    a.xplane = uint32_t(xplane);
+    a.xbatch = t.P[0] * xplane;
+    a.yrow = uint32_t(yrow);
+    a.yplane = uint32_t(yplane);
+    a.ybatch = cv.O[0] * yplane;
+    const int64_t nb = t.n * int64_t(a.NB[0]) * a.NB[1] * a.NB[2];
+    const int64_t groups = int64_t(a.nmb) * a.ncb * a.ntg;
+    if (nb >= (int64_t(1) << 30) || groups >= (int64_t(1) << 20)) return pl;
+    a.nbricks = int32_t(nb);
+    // one workgroup per CU; past 256 groups every group is its own workgroup
+    a.nsplit = int32_t(std::max<int64_t>(1, std::min<int64_t>(nb, 256 / groups)));
+    pl.part_bytes = size_t(groups) * a.nsplit * pl.wco * pl.wu * pl.nu * 4096;
+    pl.ok = true;
+    return pl;
+}
+
+template <typename T, int NU, int WCO, int WU>
+hipError_t launch_any(const AnyPlan& pl, hipStream_t s)
+{
+    const bool slow = pl.a.fold.mask != 0 || !pl.a.xvec || !pl.a.dvec;
+    const void* fn = slow ? reinterpret_cast<const void*>(&wgrad_any<T, NU, WCO, WU, true>)
+                          : reinterpret_cast<const void*>(&wgrad_any<T, NU, WCO, WU, false>);
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(pl.lds));
+    if (e != hipSuccess) return e;
+    AnyArgs a = pl.a;
+    void* args[] = {&a};
+    const unsigned grid = unsigned(int64_t(a.nmb) * a.ncb * a.ntg * a.nsplit);
+    return hipLaunchKernel(fn, dim3(grid), dim3(kThreadsA), args, pl.lds, s);
+}
+
+template <typename T, int NU>
+hipError_t launch_any_w(const AnyPlan& pl, hipStream_t s)
+{
+    if (pl.wco == 4) return launch_any<T, NU, 4, 1>(pl, s);
+    if (pl.wco == 2) return launch_any<T, NU, 2, 1>(pl, s);
+    if (pl.wu == 2) return launch_any<T, NU, 1, 2>(pl, s);
+    return launch_any<T, NU, 1, 1>(pl, s);
+}
+
+template <typename T>
+hipError_t launch_any_t(const AnyPlan& pl, hipStream_t s)
+{
+    switch (pl.nu) {
+    case 1: return launch_any_w<T, 1>(pl, s);
+    case 5: return launch_any_w<T, 5>(pl, s);
+    case 7: return launch_any_w<T, 7>(pl, s);
+    default: return launch_any_w<T, 9>(pl, s);
+    }
+}
+
+}  // namespace
+
+size_t wgrad_any_workspace(const Tile3& t, const Conv3& cv, shard_dtype_t dt)
+{
+    const AnyPlan pl = plan_any(t, cv, dt);
+    return pl.ok ? pl.part_bytes : 0;
+}
+
+hipError_t launch_wgrad_any(const Tile3& t, const Conv3& cv, shard_dtype_t dt, const void* tile, const void* dy,
+                            float* dw, void* ws, const Fold* fold, uint32_t* status, hipStream_t s)
+{
+    AnyPlan pl = plan_any(t, cv, dt);
+    if (!pl.ok) return hipErrorNotSupported;
+    AnyArgs& a = pl.a;
+    a.tile = static_cast<const char*>(tile);
+    a.dy = static_cast<const char*>(dy);
+    a.part = static_cast<float*>(ws);
+    bool xal = reinterpret_cast<uintptr_t>(tile) % 16 == 0;
+    for (int k = 0; k < 3; ++k) a.fold.P[k] = t.P[k];  // fold_voxel without a folded axis reads the tile
+    if (fold) {
+        a.fold = *fold;
+        for (int k = 0; k < 3; ++k)
+            for (int sd = 0; sd < 2; ++sd) xal = xal && reinterpret_cast<uintptr_t>(fold->slab[k][sd]) % 16 == 0;
+    }
+    const int esz = dt == SHARD_F32 ? 4 : 2;
+    a.xvec = xal && (t.c * esz) % 16 == 0;
+    a.dvec = reinterpret_cast<uintptr_t>(dy) % 16 == 0 && (cv.cout * esz) % 16 == 0;
+    hipError_t e = dt == SHARD_F32 ? launch_any_t<float>(pl, s) : launch_any_t<bf16_t>(pl, s);
+    if (e != hipSuccess) return e;
+    AnyRed r{};
+    r.part = a.part;
+    r.dw = dw;
+    r.status = status;
+    r.nsplit = a.nsplit;
+    r.nmb = a.nmb;
+    r.ncb = a.ncb;
+    r.ntg = a.ntg;
+    r.wco = pl.wco;
+    r.nu = pl.wu * pl.nu;
+    r.tpg = a.tpg;
+    r.nci = a.nci;
+    r.cin = a.cin;
+    r.cout = a.cout;
+    for (int k = 0; k < 3; ++k) {
+        r.KG[k] = a.KG[k];
+        r.NG[k] = a.NG[k];
+        r.K[k] = int32_t(cv.K[k]);
+    }
+    r.total = int64_t(a.nmb) * a.ncb * a.ntg * r.wco * r.nu * 1024;
+    void* args[] = {&r};
+    return hipLaunchKernel(reinterpret_cast<const void*>(&wgrad_any_reduce), dim3(unsigned(r.total / 64)),
+                           dim3(256), args, 0, s);
+}
+
+}  // namespace shardconv

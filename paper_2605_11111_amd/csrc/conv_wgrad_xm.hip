@@ -805,6 +805,8 @@ hipError_t launch_wgrad_xm(const Tile3& t, const Conv3& cv, shard_dtype_t dt, co
     p.a.part = static_cast<float*>(ws);
     p.a.status = status;
     p.a.wait_polls = call_opts().wait_polls ? call_opts().wait_polls : kDefaultWaitPolls;
+    const hipError_t e = launch_wgrad_status_clear(status, s);
+    if (e != hipSuccess) return e;
     return p.cfg == 0 ? run_wx<3, 1, 1, kC3BZ, kC3BY, 2, kC3NB>(p, dw, fold != nullptr, status, s)
                       : run_wx<1, 2, 2, 1, 8, 1, 2>(p, dw, fold != nullptr, status, s);
 }

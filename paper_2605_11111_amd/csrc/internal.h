@@ -183,9 +183,11 @@ size_t wgrad_xm_workspace(const Tile3& t, const Conv3& cv, shard_dtype_t dt);
 // `status`: the call's status word (see kWgradStatusBytes).
 hipError_t launch_wgrad_xm(const Tile3& t, const Conv3& cv, shard_dtype_t dt, const void* tile, const void* dy,
                            float* dw, void* ws, const Fold* fold, uint32_t* status, hipStream_t s);
-size_t wgrad_tr_workspace(const Tile3& t, const Conv3& cv, shard_dtype_t dt);
-hipError_t launch_wgrad_tr(const Tile3& t, const Conv3& cv, shard_dtype_t dt, const void* tile, const void* dy,
-                           float* part, int32_t red[6], hipStream_t s);
+// Any shape (hipErrorNotSupported: sizes past the limits of its 32-bit indices);
+// clears the call's status word.
+size_t wgrad_any_workspace(const Tile3& t, const Conv3& cv, shard_dtype_t dt);
+hipError_t launch_wgrad_any(const Tile3& t, const Conv3& cv, shard_dtype_t dt, const void* tile, const void* dy,
+                            float* dw, void* ws, const Fold* fold, uint32_t* status, hipStream_t s);
 
 // Options of the calling host thread (shard_set_call_opts): which kernel family
 // a convolution takes - the fastest applicable (default), the general tiled MFMA

@@ -198,13 +198,14 @@ shard_status_t shard_conv_fwd(const shard_tile_t* x, shard_dtype_t dtype, const 
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
  * same convolution and result, bit for bit, without the workspace arguments.
  * Its scratch (the weights rearranged for the matrix instructions) lives in a
- * static device array of the library, 4 MiB, one per GPU, held until the
+ * static device array of the library, 16 MiB, one per GPU, held until the
  * process ends; the call allocates and frees nothing. Every call on a GPU
  * shares that GPU's array, so calls that overlap on one GPU (on different
  * streams, or from different host threads) race and must be serialised by the
  * caller; sequential calls on one stream are safe.
- * Errors: as shard_conv_fwd; SHARD_ERR_UNSUPPORTED also when the workspace
- * shard_conv_fwd would need (shard_conv_workspace_bytes op 0) exceeds 4 MiB;
+ * Errors: as shard_conv_fwd; SHARD_ERR_UNSUPPORTED also when the weights laid
+ * out for the matrix instructions (channels in blocks of 32 out, of 8 in
+ * binary32 or 16 in bf16) would exceed 4 MiB in their own type;
  * SHARD_ERR_HIP also when the scratch array's address cannot be obtained.
  */
 shard_status_t shard_conv_fwd_noalloc(const shard_tile_t* x, shard_dtype_t dtype, const void* tile, const void* w,

@@ -544,7 +544,7 @@ shard_status_t shard_conv_fwd_noalloc(const shard_tile_t* x, shard_dtype_t dtype
         return SHARD_ERR_INVALID;
     if (!odd_kernel(x, kernel)) return SHARD_ERR_UNSUPPORTED;
     if (t.n * cv.out_voxels() == 0) return SHARD_OK;
-    if (conv_fwd_workspace(t, cv, dtype) > conv_fwd_noalloc_limit()) return SHARD_ERR_UNSUPPORTED;
+    if (!conv_fwd_noalloc_fits(t, cv, dtype)) return SHARD_ERR_UNSUPPORTED;
     if ((tile_elems(t) > 0 && !tile) || !w || !y) return SHARD_ERR_INVALID;
     if (!aligned(tile, t.esz) || !aligned(w, t.esz) || !aligned(y, t.esz)) return SHARD_ERR_INVALID;
     return map_hip(launch_conv_fwd_noalloc(t, cv, dtype, tile, w, y, stream));

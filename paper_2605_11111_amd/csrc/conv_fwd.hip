@@ -12,16 +12,22 @@
 // MFMA operand layout (32x32 output tile, 64 lanes, lane group g = lane/32):
 //   bf16 v_mfma_f32_32x32x16_bf16: lane holds 8 consecutive K (= 8 channels of
 //        one voxel) for row lane%32 -> one 16-byte LDS read per lane.
-//   f32  v_mfma_f32_32x32x2_f32: lane holds 1 K value; four MFMAs consume one
-//        16-byte read of 4 consecutive channels (K order permuted so that lane
-//        group g of step s holds channel 8*c + 4*g + s in both operands).
+// binary32 data is split into three bf16 parts (split_bf16x3: the brick while it
+// is staged, the weights when their fragments are laid out) and multiplied by
+// six of those MFMAs per product: 192 cycles per 16 channels against 512 on
+// v_mfma_f32_32x32x2_f32. The products of two iterations are summed from zero
+// and then added to the accumulators (the MFMA aligns its products to its addend
+// with fewer bits than binary32 has), every other pair with the weights negated
+// and subtracted (what the MFMA cuts off has a mean, which cancels).
 // The B operand (weights) is pre-arranged by `wfrag_kernel` so that one
 // coalesced 1 KiB load per wave yields a ready fragment.
 //
-// LDS layout: voxel v of the input brick occupies NQ 16-byte units, stored
-// unit-major: unit q of voxel v at q * NV + v (NV the brick's voxels), so that
-// lanes reading consecutive voxels read consecutive 16-byte words and a lane's
-// address for a tap is its own fixed part plus a uniform offset.
+// LDS layout: voxel v of the input brick occupies NQ units of eight channels, each
+// one 16-byte word per part (one part for bf16, three for binary32), stored
+// unit-major: part p of unit q of voxel v at (q * parts + p) * NV + v (NV the
+// brick's voxels), so that lanes reading consecutive voxels read consecutive
+// 16-byte words and a lane's address for a tap is its own fixed part plus a
+// uniform offset.
 #include <algorithm>
 #include <cstdlib>
 #include <type_traits>
@@ -50,7 +56,9 @@ struct FwdArgs {
     int32_t BO[3];     // output brick
     int32_t BI[3];     // input brick
     int32_t NB[3];     // bricks per axis
-    int32_t nq;        // 16-byte units per voxel in LDS (per pass)
+    int32_t nq;        // 8-channel units per voxel in LDS (per pass)
+    int32_t kdp;       // planes of taps along D per pass: K[0], or 1 (only the planes that one kd
+                       // meets are staged, BI[0] = BO[0] of them, S[0] apart)
     int32_t cc;        // channels per pass
     int32_t npass;
     int32_t nkc;       // K-chunks over all input channels
@@ -76,38 +84,96 @@ struct FwdLaunch {
 };
 
 struct PlanF {
-    int rm, rn;
+    int rm, rn, wn;
+    double cost;
     FwdArgs a;
     size_t lds;
     bool ok;
 };
 
+constexpr int kc = 16;  // channels per MFMA K-chunk
+
 template <typename T>
 struct Traits;
 template <>
 struct Traits<bf16_t> {
-    static constexpr int kc = 16;  // channels per MFMA K-chunk
     static constexpr int esz = 2;
+    static constexpr int parts = 1;
 };
 template <>
 struct Traits<float> {
-    static constexpr int kc = 8;
     static constexpr int esz = 4;
+    static constexpr int parts = 3;
 };
 
-// Stage every 16-byte unit (voxel v = (z, y, x) of the brick, channel unit q)
-// once across the block: fetch(v, q, z, y, x) gives its value, stored at
-// lds[q * nvp + v]. A thread fetches kStageBatch units before it stores them,
+// Eight channels of a voxel as loaded from memory.
+template <typename T>
+struct Unit {
+    uint4 v[Traits<T>::esz / 2];
+};
+
+template <typename T>
+__device__ __forceinline__ Unit<T> zero_unit()
+{
+    Unit<T> u;
+#pragma unroll
+    for (int i = 0; i < Traits<T>::esz / 2; ++i) u.v[i] = make_uint4(0, 0, 0, 0);
+    return u;
+}
+
+// A whole unit at a 16-byte aligned address.
+template <typename T>
+__device__ __forceinline__ Unit<T> load_unit(const char* p)
+{
+    Unit<T> u;
+#pragma unroll
+    for (int i = 0; i < Traits<T>::esz / 2; ++i) u.v[i] = reinterpret_cast<const uint4*>(p)[i];
+    return u;
+}
+
+// Channels c .. c + 7 of the voxel at `src` (its channel c; zeros past cin).
+template <typename T>
+__device__ __forceinline__ Unit<T> load_channels(const T* src, int c, int64_t cin, bool vec_ok)
+{
+    if (vec_ok && c + 8 <= cin) return load_unit<T>(reinterpret_cast<const char*>(src));
+    T tmp[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) tmp[e] = (c + e < cin) ? src[e] : T(0);
+    Unit<T> u;
+    __builtin_memcpy(&u, tmp, sizeof(u));
+    return u;
+}
+
+// Store a unit's parts at dst, dst + nvp, ... (16-byte words).
+template <typename T>
+__device__ __forceinline__ void store_unit(uint4* dst, int nvp, const Unit<T>& u)
+{
+    if constexpr (Traits<T>::parts == 1) {
+        *dst = u.v[0];
+    } else {
+        float f[8];
+        __builtin_memcpy(f, &u, sizeof(f));
+        uint4 hi, mid, lo;
+        split_bf16x3(f, hi, mid, lo);
+        dst[0] = hi;
+        dst[nvp] = mid;
+        dst[2 * nvp] = lo;
+    }
+}
+
+// Stage every unit (voxel v = (z, y, x) of the brick, channel unit q) once
+// across the block: fetch(v, q, z, y, x) gives its value, whose parts are stored
+// at lds[(q * parts + p) * nvp + v]. A thread fetches kStageBatch units before it stores them,
 // so that their loads are in flight together (one at a time, each store
 // waited for its load). When a (z, y) row of units fits the block, a thread
 // keeps its column (x, q) and steps over rows: one division per row instead of
 // three per unit.
 constexpr int kStageBatch = 4;
 
-template <typename F>
+template <typename T, typename F>
 __device__ __forceinline__ void stage_units(const FwdArgs& a, uint4* lds, int nvp, F&& fetch)
 {
-    constexpr int B = kStageBatch;
+    constexpr int B = kStageBatch, PT = Traits<T>::parts;
     const int nq = a.nq;
     const int rowlen = a.BI[2] * nq;
     if (rowlen <= kThreads) {
@@ -117,11 +183,11 @@ __device__ __forceinline__ void stage_units(const FwdArgs& a, uint4* lds, int nv
         const int x = cu / nq, q = cu - x * nq;
         const int rows = a.BI[0] * a.BI[1];
         for (int r = r0; r < rows; r += B * rpp) {
-            uint4 val[B];
+            Unit<T> val[B];
 #pragma unroll
             for (int j = 0; j < B; ++j) {
                 const int rr = r + j * rpp;
-                val[j] = make_uint4(0, 0, 0, 0);
+                val[j] = zero_unit<T>();
                 if (rr < rows) {
                     const int z = rr / a.BI[1], y = rr - z * a.BI[1];
                     val[j] = fetch(rr * a.BI[2] + x, q, z, y, x);
@@ -130,18 +196,18 @@ __device__ __forceinline__ void stage_units(const FwdArgs& a, uint4* lds, int nv
 #pragma unroll
             for (int j = 0; j < B; ++j) {
                 const int rr = r + j * rpp;
-                if (rr < rows) lds[q * nvp + rr * a.BI[2] + x] = val[j];
+                if (rr < rows) store_unit<T>(lds + q * PT * nvp + rr * a.BI[2] + x, nvp, val[j]);
             }
         }
         return;
     }
     const int total = a.BI[0] * a.BI[1] * a.BI[2] * nq;
     for (int u = threadIdx.x; u < total; u += B * kThreads) {
-        uint4 val[B];
+        Unit<T> val[B];
 #pragma unroll
         for (int j = 0; j < B; ++j) {
             const int uu = u + j * kThreads;
-            val[j] = make_uint4(0, 0, 0, 0);
+            val[j] = zero_unit<T>();
             if (uu < total) {
                 const int q = uu % nq, v = uu / nq;
                 const int x = v % a.BI[2], yz = v / a.BI[2];
@@ -151,7 +217,7 @@ __device__ __forceinline__ void stage_units(const FwdArgs& a, uint4* lds, int nv
 #pragma unroll
         for (int j = 0; j < B; ++j) {
             const int uu = u + j * kThreads;
-            if (uu < total) lds[(uu % nq) * nvp + uu / nq] = val[j];
+            if (uu < total) store_unit<T>(lds + (uu % nq) * PT * nvp + uu / nq, nvp, val[j]);
         }
     }
 }
@@ -169,9 +235,9 @@ __device__ __forceinline__ void stage_units(const FwdArgs& a, uint4* lds, int nv
 // buffer; along D or H the row does, and its offset is formed per unit.
 template <typename T, int B, int FK>
 __device__ __forceinline__ void stage_rows(const FwdArgs& a, uint4* lds, int nvp, int64_t nn, const int64_t i0[3],
-                                           int c0)
+                                           int c0, int zs)
 {
-    constexpr int kPerUnit = 16 / Traits<T>::esz;
+    constexpr int kPerUnit = 8;
     constexpr int64_t esz = Traits<T>::esz;
     // the thread's column is formed anew in every pass (an opaque copy of the
     // thread index), so that none of this stays live across the MFMA loop
@@ -205,10 +271,15 @@ __device__ __forceinline__ void stage_rows(const FwdArgs& a, uint4* lds, int nvp
         u2 = hi ? t2 - hik : t2;
     }
     const bool colok = t2 >= 0 && t2 < a.P[2] && c < a.cin && src != nullptr;
-    // rows z of the brick with i0[0] + z inside the tile are [zlo, zhi); same for y
+    // rows y of the brick with i0[1] + y inside the tile are [ylo, yhi); planes z
+    // (zs tile planes apart, from i0[0]) are inside when zt0 + z zs is in [0, P0)
     const int BI0 = a.BI[0], BI1 = a.BI[1];
-    const int zlo = int(std::min<int64_t>(std::max<int64_t>(-i0[0], 0), BI0));
-    const int zhi = int(std::min<int64_t>(std::max<int64_t>(a.P[0] - i0[0], 0), BI0));
+    int zlo = int(std::min<int64_t>(std::max<int64_t>(-i0[0], 0), int64_t(BI0) * zs));
+    int zhi = int(std::min<int64_t>(std::max<int64_t>(a.P[0] - i0[0], 0), int64_t(BI0) * zs));
+    if constexpr (Traits<T>::parts > 1) {
+        zlo = (zlo + zs - 1) / zs;
+        zhi = (zhi + zs - 1) / zs;
+    }
     const int ylo = int(std::min<int64_t>(std::max<int64_t>(-i0[1], 0), BI1));
     const int yhi = int(std::min<int64_t>(std::max<int64_t>(a.P[1] - i0[1], 0), BI1));
     // byte offset of unit (z, y) of the column in its buffer:
@@ -216,29 +287,29 @@ __device__ __forceinline__ void stage_rows(const FwdArgs& a, uint4* lds, int nvp
     const int64_t rowb = e2 * vb, colb = u2 * vb + int64_t(c) * esz;
     const int dz = rpp / BI1, dy = rpp - dz * BI1;
     int z = r0 / BI1, y = r0 - z * BI1;
-    int64_t off = ((nn * a.P[0] + i0[0] + z) * a.P[1] + i0[1] + y) * rowb + colb;
-    const int64_t step = (int64_t(dz) * a.P[1] + dy) * rowb, wrap = (a.P[1] - BI1) * rowb;
+    int64_t off = ((nn * a.P[0] + i0[0] + int64_t(z) * zs) * a.P[1] + i0[1] + y) * rowb + colb;
+    const int64_t step = (int64_t(dz) * zs * a.P[1] + dy) * rowb, wrap = (zs * a.P[1] - BI1) * rowb;
     const int rows = BI0 * BI1;
     const int dstep = rpp * a.BI[2];
-    uint4* dst = lds + q * nvp + r0 * a.BI[2] + x;
+    uint4* dst = lds + q * Traits<T>::parts * nvp + r0 * a.BI[2] + x;
     for (int r = r0; r < rows; r += B * rpp) {
-        uint4 val[B];
+        Unit<T> val[B];
 #pragma unroll
         for (int j = 0; j < B; ++j) {
-            val[j] = make_uint4(0, 0, 0, 0);
+            val[j] = zero_unit<T>();
             if (r + j * rpp < rows && colok && z >= zlo && z < zhi && y >= ylo && y < yhi) {
                 if constexpr (FK == 0 || FK == 1) {
                     // the row's buffer: the row index in it times the row bytes
-                    const int64_t t0 = i0[0] + z, t1 = i0[1] + y;
+                    const int64_t t0 = i0[0] + int64_t(z) * zs, t1 = i0[1] + y;
                     const int64_t tk = FK == 0 ? t0 : t1;
                     const bool lo = tk < lok, hi = tk >= hik;
                     const char* base = lo ? slo : (hi ? shi : a.tile);
                     const int64_t ek = lo ? lok : (hi ? a.P[FK] - hik : a.P[FK]);
                     const int64_t ck = hi ? tk - hik : tk;
                     const int64_t row = FK == 0 ? (nn * ek + ck) * a.P[1] + t1 : (nn * a.P[0] + t0) * ek + ck;
-                    if (base) val[j] = *reinterpret_cast<const uint4*>(base + row * rowb + colb);
+                    if (base) val[j] = load_unit<T>(base + row * rowb + colb);
                 } else {
-                    val[j] = *reinterpret_cast<const uint4*>(src + off);
+                    val[j] = load_unit<T>(src + off);
                 }
             }
             z += dz;
@@ -252,7 +323,7 @@ __device__ __forceinline__ void stage_rows(const FwdArgs& a, uint4* lds, int nvp
         }
 #pragma unroll
         for (int j = 0; j < B; ++j)
-            if (r + j * rpp < rows) dst[j * dstep] = val[j];
+            if (r + j * rpp < rows) store_unit<T>(dst + j * dstep, nvp, val[j]);
         dst += B * dstep;
     }
 }
@@ -260,9 +331,10 @@ __device__ __forceinline__ void stage_rows(const FwdArgs& a, uint4* lds, int nvp
 // Stage the input brick channels [c0, c0 + cc) into LDS; SB units in flight
 // per thread on the row paths.
 template <typename T, int SB>
-__device__ __forceinline__ void stage_brick(const FwdArgs& a, uint4* lds, int64_t nn, const int64_t i0[3], int c0)
+__device__ __forceinline__ void stage_brick(const FwdArgs& a, uint4* lds, int64_t nn, const int64_t i0[3], int c0,
+                                            int zs)
 {
-    constexpr int kPerUnit = 16 / Traits<T>::esz;
+    constexpr int kPerUnit = 8;
     const bool vec_ok = a.vec != 0;
     const int nvp = a.BI[0] * a.BI[1] * a.BI[2];  // voxels per unit plane
     // a brick whose footprint (clipped to the tile) stays off every folded
@@ -271,18 +343,19 @@ __device__ __forceinline__ void stage_brick(const FwdArgs& a, uint4* lds, int64_
     for (int k = 0; k < 3; ++k) {
         if (!((a.fold.mask >> k) & 1u)) continue;
         const int64_t f0 = i0[k] > 0 ? i0[k] : 0;
-        const int64_t f1 = i0[k] + a.BI[k] < a.P[k] ? i0[k] + a.BI[k] : a.P[k];
+        const int64_t e = k == 0 ? (a.BI[0] - 1) * int64_t(zs) + 1 : a.BI[k];
+        const int64_t f1 = i0[k] + e < a.P[k] ? i0[k] + e : a.P[k];
         margin = margin || (f0 < f1 && (f0 < a.fold.lo[k] || f1 > a.fold.lo[k] + a.fold.ext[k]));
     }
     const uint32_t fm = a.fold.mask;
     const bool rows_ok = vec_ok && a.cin % kPerUnit == 0 && a.BI[2] * a.nq <= kThreads;
     if (margin && rows_ok && (fm == 1u || fm == 2u || fm == 4u)) {
         if (fm == 1u)
-            stage_rows<T, SB, 0>(a, lds, nvp, nn, i0, c0);
+            stage_rows<T, SB, 0>(a, lds, nvp, nn, i0, c0, zs);
         else if (fm == 2u)
-            stage_rows<T, SB, 1>(a, lds, nvp, nn, i0, c0);
+            stage_rows<T, SB, 1>(a, lds, nvp, nn, i0, c0, zs);
         else
-            stage_rows<T, SB, 2>(a, lds, nvp, nn, i0, c0);
+            stage_rows<T, SB, 2>(a, lds, nvp, nn, i0, c0, zs);
         return;
     }
     if (margin && (fm == 1u || fm == 2u || fm == 4u)) {
@@ -293,10 +366,10 @@ __device__ __forceinline__ void stage_brick(const FwdArgs& a, uint4* lds, int64_
         const char* slo = a.fold.slab[k][0];
         const char* shi = a.fold.slab[k][1];
         const int64_t vb = a.cin * Traits<T>::esz;
-        stage_units(a, lds, nvp, [&](int v, int q, int z, int y, int x) {
-            const int64_t t0 = i0[0] + z, t1 = i0[1] + y, t2 = i0[2] + x;
+        stage_units<T>(a, lds, nvp, [&](int v, int q, int z, int y, int x) {
+            const int64_t t0 = i0[0] + int64_t(z) * zs, t1 = i0[1] + y, t2 = i0[2] + x;
             const int c = c0 + q * kPerUnit;
-            uint4 val = make_uint4(0, 0, 0, 0);
+            Unit<T> val = zero_unit<T>();
             if (t0 >= 0 && t0 < a.P[0] && t1 >= 0 && t1 < a.P[1] && t2 >= 0 && t2 < a.P[2] && c < a.cin) {
                 const int64_t tk = k == 0 ? t0 : (k == 1 ? t1 : t2);
                 const bool lo = tk < lok, hi = tk >= hik;
@@ -308,14 +381,7 @@ __device__ __forceinline__ void stage_brick(const FwdArgs& a, uint4* lds, int64_
                 const int64_t u0 = k == 0 ? ck : t0, u1 = k == 1 ? ck : t1, u2 = k == 2 ? ck : t2;
                 if (base) {
                     const T* src = reinterpret_cast<const T*>(base + (((nn * d0 + u0) * e1 + u1) * e2 + u2) * vb) + c;
-                    if (vec_ok && c + kPerUnit <= a.cin) {
-                        val = *reinterpret_cast<const uint4*>(src);
-                    } else {
-                        T tmp[kPerUnit];
-#pragma unroll
-                        for (int e = 0; e < kPerUnit; ++e) tmp[e] = (c + e < a.cin) ? src[e] : T(0);
-                        val = *reinterpret_cast<const uint4*>(tmp);
-                    }
+                    val = load_channels<T>(src, c, a.cin, vec_ok);
                 }
             }
             return val;
@@ -324,22 +390,15 @@ __device__ __forceinline__ void stage_brick(const FwdArgs& a, uint4* lds, int64_
     }
     if (margin) {
         // margin voxels come from the received slabs (or are zero)
-        stage_units(a, lds, nvp, [&](int v, int q, int z, int y, int x) {
-            const int64_t t0 = i0[0] + z, t1 = i0[1] + y, t2 = i0[2] + x;
+        stage_units<T>(a, lds, nvp, [&](int v, int q, int z, int y, int x) {
+            const int64_t t0 = i0[0] + int64_t(z) * zs, t1 = i0[1] + y, t2 = i0[2] + x;
             const int c = c0 + q * kPerUnit;
-            uint4 val = make_uint4(0, 0, 0, 0);
+            Unit<T> val = zero_unit<T>();
             if (t0 >= 0 && t0 < a.P[0] && t1 >= 0 && t1 < a.P[1] && t2 >= 0 && t2 < a.P[2] && c < a.cin) {
                 const char* vox = fold_voxel(a.fold, a.tile, nn, t0, t1, t2, a.cin * Traits<T>::esz);
                 if (vox) {
                     const T* src = reinterpret_cast<const T*>(vox) + c;
-                    if (vec_ok && c + kPerUnit <= a.cin) {
-                        val = *reinterpret_cast<const uint4*>(src);
-                    } else {
-                        T tmp[kPerUnit];
-#pragma unroll
-                        for (int e = 0; e < kPerUnit; ++e) tmp[e] = (c + e < a.cin) ? src[e] : T(0);
-                        val = *reinterpret_cast<const uint4*>(tmp);
-                    }
+                    val = load_channels<T>(src, c, a.cin, vec_ok);
                 }
             }
             return val;
@@ -347,50 +406,30 @@ __device__ __forceinline__ void stage_brick(const FwdArgs& a, uint4* lds, int64_
         return;
     }
     if (rows_ok) {
-        stage_rows<T, SB, -1>(a, lds, nvp, nn, i0, c0);
+        stage_rows<T, SB, -1>(a, lds, nvp, nn, i0, c0, zs);
         return;
     }
-    stage_units(a, lds, nvp, [&](int v, int q, int z, int y, int x) {
-        const int64_t t0 = i0[0] + z, t1 = i0[1] + y, t2 = i0[2] + x;
+    stage_units<T>(a, lds, nvp, [&](int v, int q, int z, int y, int x) {
+        const int64_t t0 = i0[0] + int64_t(z) * zs, t1 = i0[1] + y, t2 = i0[2] + x;
         const int c = c0 + q * kPerUnit;
-        uint4 val = make_uint4(0, 0, 0, 0);
+        Unit<T> val = zero_unit<T>();
         if (t0 >= 0 && t0 < a.P[0] && t1 >= 0 && t1 < a.P[1] && t2 >= 0 && t2 < a.P[2] && c < a.cin) {
             const int64_t off = ((((nn * a.P[0] + t0) * a.P[1] + t1) * a.P[2] + t2) * a.cin + c) * Traits<T>::esz;
-            if (vec_ok && c + kPerUnit <= a.cin) {
-                val = *reinterpret_cast<const uint4*>(a.tile + off);
-            } else {
-                T tmp[kPerUnit];
-                const T* src = reinterpret_cast<const T*>(a.tile + off);
-#pragma unroll
-                for (int e = 0; e < kPerUnit; ++e) tmp[e] = (c + e < a.cin) ? src[e] : T(0);
-                val = *reinterpret_cast<const uint4*>(tmp);
-            }
+            val = load_channels<T>(reinterpret_cast<const T*>(a.tile + off), c, a.cin, vec_ok);
         }
         return val;
     });
 }
 
-template <typename T>
-__device__ __forceinline__ void mfma_step(f32x16_t& acc, uint4 av, uint4 bv);
-
-template <>
-__device__ __forceinline__ void mfma_step<bf16_t>(f32x16_t& acc, uint4 av, uint4 bv)
+__device__ __forceinline__ f32x16_t mfma(uint4 av, uint4 bv, const f32x16_t& c)
 {
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, av), __builtin_bit_cast(bf16x8_t, bv),
-                                                   acc, 0, 0, 0);
-}
-
-template <>
-__device__ __forceinline__ void mfma_step<float>(f32x16_t& acc, uint4 av, uint4 bv)
-{
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(av.x), __uint_as_float(bv.x), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(av.y), __uint_as_float(bv.y), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(av.z), __uint_as_float(bv.z), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(av.w), __uint_as_float(bv.w), acc, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, av), __builtin_bit_cast(bf16x8_t, bv), c,
+                                                   0, 0, 0);
 }
 
 // Brick b (in the XCD-aware order) of one region.
-template <typename T, int RM, int RN>
+// The four waves are 4 / WN along M and WN along N.
+template <typename T, int RM, int RN, int WN>
 __device__ __forceinline__ void fwd_tiled_body(const FwdArgs& a, int64_t b)
 {
     extern __shared__ uint4 lds[];
@@ -411,7 +450,13 @@ __device__ __forceinline__ void fwd_tiled_body(const FwdArgs& a, int64_t b)
     const int64_t ob[3] = {int64_t(bz) * a.BO[0], int64_t(by) * a.BO[1], int64_t(bx) * a.BO[2]};
     const int64_t i0[3] = {(a.org[0] + ob[0]) * a.S[0] - a.pad[0], (a.org[1] + ob[1]) * a.S[1] - a.pad[1],
                            (a.org[2] + ob[2]) * a.S[2] - a.pad[2]};
-    const int nt0 = ngi * RN;
+    constexpr int PT = Traits<T>::parts;
+    const int wm = wave / WN, wn = wave % WN;
+    const int nt0 = (ngi * WN + wn) * RN;
+    // one plane of taps per pass (binary32 alone): tile planes between staged
+    // planes, staged planes between output planes
+    const bool kdsplit = PT > 1 && a.kdp < a.K[0];
+    const int zs = kdsplit ? a.S[0] : 1, zo = kdsplit ? 1 : a.S[0];
     const int bov = a.BO[0] * a.BO[1] * a.BO[2];
 
     // per-lane LDS voxel base of each of this wave's M tiles. A-row `row` of a
@@ -422,12 +467,12 @@ __device__ __forceinline__ void fwd_tiled_body(const FwdArgs& a, int64_t b)
     int vbase[RM];
 #pragma unroll
     for (int i = 0; i < RM; ++i) {
-        const int f = (wave * RM + i) * 32 + prow;
+        const int f = (wm * RM + i) * 32 + prow;
         const int ff = f < bov ? f : 0;
         const int ox = ff % a.BO[2];
         const int oy = (ff / a.BO[2]) % a.BO[1];
         const int oz = ff / (a.BO[2] * a.BO[1]);
-        vbase[i] = (oz * a.S[0] * a.BI[1] + oy * a.S[1]) * a.BI[2] + ox * a.S[2];
+        vbase[i] = (oz * zo * a.BI[1] + oy * a.S[1]) * a.BI[2] + ox * a.S[2];
     }
 
     f32x16_t acc[RM][RN];
@@ -438,14 +483,23 @@ __device__ __forceinline__ void fwd_tiled_body(const FwdArgs& a, int64_t b)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    const int taps = a.K[0] * a.K[1] * a.K[2];
-    const int kcp = a.cc / Traits<T>::kc;  // K-chunks per pass
+    const int ptaps = (kdsplit ? 1 : a.K[0]) * a.K[1] * a.K[2];  // taps per pass
+    const int kcp = a.cc / kc;                  // K-chunks per pass
     const int plane = a.BI[1] * a.BI[2];
-    for (int p = 0; p < a.npass; ++p) {
-        if (p > 0) __syncthreads();
-        stage_brick<T, kStageBatch>(a, lds, nn, i0, p * a.cc);
+    const int npasses = kdsplit ? a.npass * a.K[0] : a.npass;
+    for (int pp = 0; pp < npasses; ++pp) {
+        // channel pass p, first tap plane kd0; the channel passes of a plane
+        // follow each other, while the lines that they share are in the L2
+        const int kd0 = PT == 1 ? 0 : pp / a.npass, p = PT == 1 ? pp : pp - kd0 * a.npass;
+        if (pp > 0) __syncthreads();
+        if constexpr (PT == 1) {
+            stage_brick<T, kStageBatch>(a, lds, nn, i0, p * a.cc, 1);
+        } else {
+            const int64_t ik[3] = {i0[0] + kd0, i0[1], i0[2]};
+            stage_brick<T, RN == 1 ? kStageBatch : kStageBatch / 2>(a, lds, nn, ik, p * a.cc, zs);
+        }
         __syncthreads();
-        const int iters = taps * kcp;
+        const int iters = ptaps * kcp;
         // Iteration = (tap, channel chunk). Software pipeline over two operand
         // sets that alternate (no register copies): the A fragments (LDS) and B
         // fragments (weights, L2) of iteration it + 1 are in flight while
@@ -462,8 +516,9 @@ __device__ __forceinline__ void fwd_tiled_body(const FwdArgs& a, int64_t b)
             int toff;        // brick voxel offset of the tap
             int kc, t2, t1;
         };
-        const int64_t ks = int64_t(a.nt) * 64;                 // one K-chunk
-        const int64_t ts = int64_t(a.nkc - kcp) * a.nt * 64;  // the other passes' chunks
+        const int64_t ks = int64_t(a.nt) * 64 * PT;                 // one K-chunk
+        const int64_t ts = int64_t(a.nkc - kcp) * a.nt * 64 * PT;  // the other passes' chunks
+        const int64_t ps = int64_t(a.nt) * 64;                      // one part of a K-chunk
         const int wrap2 = a.BI[2] - a.K[2], wrap1 = plane - a.K[1] * a.BI[2];
         auto step_tap = [&](TapIt& s) {
             s.b += ks;
@@ -487,33 +542,78 @@ __device__ __forceinline__ void fwd_tiled_body(const FwdArgs& a, int64_t b)
         const uint32_t plane16 = uint32_t(a.BI[0] * a.BI[1] * a.BI[2]) * 16u;
         uint32_t abase[RM];
 #pragma unroll
-        for (int i = 0; i < RM; ++i) abase[i] = uint32_t(g) * plane16 + uint32_t(vbase[i]) * 16u;
-        auto load = [&](const TapIt& s, uint4 (&av)[RM], uint4 (&bv)[RN]) {
+        for (int i = 0; i < RM; ++i) abase[i] = uint32_t(g * PT) * plane16 + uint32_t(vbase[i]) * 16u;
+        auto load = [&](const TapIt& s, uint4 (&av)[RM][PT], uint4 (&bv)[RN][PT]) {
 #pragma unroll
-            for (int j = 0; j < RN; ++j) bv[j] = s.b[j * 64 + lane];
-            const uint32_t u = uint32_t(2 * s.kc) * plane16 + uint32_t(s.toff) * 16u;
+            for (int q = 0; q < PT; ++q)
 #pragma unroll
-            for (int i = 0; i < RM; ++i) av[i] = *reinterpret_cast<const uint4*>(ldsb + (abase[i] + u));
+                for (int j = 0; j < RN; ++j) bv[j][q] = s.b[q * ps + j * 64 + lane];
+            const uint32_t u = uint32_t(2 * PT * s.kc) * plane16 + uint32_t(s.toff) * 16u;
+#pragma unroll
+            for (int q = 0; q < PT; ++q)
+#pragma unroll
+                for (int i = 0; i < RM; ++i)
+                    av[i][q] = *reinterpret_cast<const uint4*>(ldsb + (abase[i] + u + uint32_t(q) * plane16));
         };
-        auto mma = [&](const uint4 (&av)[RM], const uint4 (&bv)[RN]) {
-#pragma unroll
-            for (int i = 0; i < RM; ++i)
-#pragma unroll
-                for (int j = 0; j < RN; ++j) mfma_step<T>(acc[i][j], av[i], bv[j]);
-        };
-        TapIt nx{a.wfrag + (int64_t(p) * kcp * a.nt + nt0) * 64, 0, 0, 0, 0};
-        uint4 a0[RM], b0[RN], a1[RM], b1[RN];
+        TapIt nx{a.wfrag + ((int64_t(PT > 1 ? kd0 : 0) * a.K[1] * a.K[2] * a.nkc + int64_t(p) * kcp) * a.nt * PT + nt0) * 64,
+                 0, 0, 0, 0};
+        uint4 a0[RM][PT], b0[RN][PT], a1[RM][PT], b1[RN][PT];
         load(nx, a0, b0);
         int it = 0;
-        for (; it + 1 < iters; it += 2) {
-            step_tap(nx);
-            load(nx, a1, b1);  // iteration it + 1
-            mma(a0, b0);
-            if (it + 2 < iters) step_tap(nx);
-            load(nx, a0, b0);  // iteration it + 2 (past the end: it + 1 again)
-            mma(a1, b1);
+        if constexpr (PT == 1) {
+            auto mma = [&](const uint4 (&av)[RM][PT], const uint4 (&bv)[RN][PT]) {
+#pragma unroll
+                for (int i = 0; i < RM; ++i)
+#pragma unroll
+                    for (int j = 0; j < RN; ++j) acc[i][j] = mfma(av[i][0], bv[j][0], acc[i][j]);
+            };
+            for (; it + 1 < iters; it += 2) {
+                step_tap(nx);
+                load(nx, a1, b1);  // iteration it + 1
+                mma(a0, b0);
+                if (it + 2 < iters) step_tap(nx);
+                load(nx, a0, b0);  // iteration it + 2 (past the end: it + 1 again)
+                mma(a1, b1);
+            }
+            if (it < iters) mma(a0, b0);
+        } else {
+            // the pair's products from zero (small ones first), then added with
+            // the pair's sign (the weights of odd pairs are laid out negated)
+            f32x16_t t[RM][RN];
+            auto mma = [&](const uint4 (&av)[RM][PT], const uint4 (&bv)[RN][PT], bool first) {
+                constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+                for (int q = 0; q < 6; ++q)
+#pragma unroll
+                    for (int i = 0; i < RM; ++i)
+#pragma unroll
+                        for (int j = 0; j < RN; ++j)
+                            t[i][j] = mfma(av[i][pa[q]], bv[j][pb[q]], first && q == 0 ? f32x16_t{} : t[i][j]);
+            };
+            float sgn = 1.f;
+            auto add = [&]() {
+#pragma unroll
+                for (int i = 0; i < RM; ++i)
+#pragma unroll
+                    for (int j = 0; j < RN; ++j)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) acc[i][j][e] = fmaf(t[i][j][e], sgn, acc[i][j][e]);
+                sgn = -sgn;
+            };
+            for (; it + 1 < iters; it += 2) {
+                step_tap(nx);
+                load(nx, a1, b1);
+                mma(a0, b0, true);
+                if (it + 2 < iters) step_tap(nx);
+                load(nx, a0, b0);
+                mma(a1, b1, false);
+                add();
+            }
+            if (it < iters) {
+                mma(a0, b0, true);
+                add();
+            }
         }
-        if (it < iters) mma(a0, b0);
     }
 
     // epilogue: lane holds column lane%32, rows 8*(r/4) + 4*g + (r%4). The
@@ -538,7 +638,7 @@ __device__ __forceinline__ void fwd_tiled_body(const FwdArgs& a, int64_t b)
         const int crow = lane / CPR, ccol = (lane % CPR) * VE;
 #pragma unroll
         for (int i = 0; i < RM; ++i) {
-            const int f0 = (wave * RM + i) * 32 + crow;
+            const int f0 = (wm * RM + i) * 32 + crow;
             int ox0 = f0 % a.BO[2], oy0 = (f0 / a.BO[2]) % a.BO[1], oz0 = f0 / (a.BO[2] * a.BO[1]);
 #pragma unroll
             for (int j = 0; j < RN; ++j) {
@@ -588,7 +688,7 @@ __device__ __forceinline__ void fwd_tiled_body(const FwdArgs& a, int64_t b)
     // advanced from the previous row's (carries instead of divisions)
 #pragma unroll
     for (int i = 0; i < RM; ++i) {
-        const int fb = (wave * RM + i) * 32 + 4 * g;
+        const int fb = (wm * RM + i) * 32 + 4 * g;
         int ox = fb % a.BO[2];
         int oy = (fb / a.BO[2]) % a.BO[1];
         int oz = fb / (a.BO[2] * a.BO[1]);
@@ -617,107 +717,120 @@ __device__ __forceinline__ void fwd_tiled_body(const FwdArgs& a, int64_t b)
     }
 }
 
-template <typename T, int RM, int RN>
+template <typename T, int RM, int RN, int WN>
 __global__ __launch_bounds__(kThreads, 2) void conv_fwd_tiled(FwdArgs a)
 {
-    fwd_tiled_body<T, RM, RN>(a, xcd_remap(blockIdx.x, a.nblocks));
+    fwd_tiled_body<T, RM, RN, WN>(a, xcd_remap(blockIdx.x, a.nblocks));
 }
 
 // Several regions in one launch: each takes its own inlined copy of the body,
 // so that its arguments are read from a fixed place.
-template <typename T, int RM, int RN>
+template <typename T, int RM, int RN, int WN>
 __global__ __launch_bounds__(kThreads, 2) void conv_fwd_tiledn(FwdLaunch la)
 {
     const int64_t b = xcd_remap(blockIdx.x, gridDim.x);
     if (b < la.end[0])
-        fwd_tiled_body<T, RM, RN>(la.r[0], b);
+        fwd_tiled_body<T, RM, RN, WN>(la.r[0], b);
     else if (b < la.end[1])
-        fwd_tiled_body<T, RM, RN>(la.r[1], b - la.end[0]);
+        fwd_tiled_body<T, RM, RN, WN>(la.r[1], b - la.end[0]);
     else if (b < la.end[2])
-        fwd_tiled_body<T, RM, RN>(la.r[2], b - la.end[1]);
+        fwd_tiled_body<T, RM, RN, WN>(la.r[2], b - la.end[1]);
     else
-        fwd_tiled_body<T, RM, RN>(la.r[3], b - la.end[2]);
+        fwd_tiled_body<T, RM, RN, WN>(la.r[3], b - la.end[2]);
 }
 
-// wfrag[((tap * nkc + kc) * nt + ntile) * 64 + lane] = 16 bytes of weights in
-// MFMA B-fragment order (see the file comment); zero past cin / cout.
+// wfrag[(((tap * nkc + chunk) * parts + part) * nt + ntile) * 64 + lane] = 16 bytes
+// of weights in MFMA B-fragment order (see the file comment); zero past cin /
+// cout. binary32: the three parts, negated in every other pair of the iterations
+// (kd, kh, kw, chunk) of a pass of ptaps taps and kcp chunks.
 template <typename T>
 __global__ __launch_bounds__(256) void wfrag_kernel(const T* w, uint4* wfrag, int64_t cin, int64_t cout, int taps,
-                                                    int nkc, int nt)
+                                                    int nkc, int nt, int ptaps, int kcp)
 {
-    constexpr int kPer = 16 / Traits<T>::esz;
+    constexpr int PT = Traits<T>::parts;
     const int64_t total = int64_t(taps) * nkc * nt * 64;
     for (int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x; e < total; e += int64_t(gridDim.x) * 256) {
         const int lane = int(e % 64);
         int64_t r = e / 64;
         const int ntile = int(r % nt);
         r /= nt;
-        const int kc = int(r % nkc);
+        const int chunk = int(r % nkc);
         const int tap = int(r / nkc);
         const int64_t co = int64_t(ntile) * 32 + (lane & 31);
         const int g = lane >> 5;
-        T vals[kPer];
+        T vals[8];
 #pragma unroll
-        for (int s = 0; s < kPer; ++s) {
-            const int64_t ci = int64_t(kc) * Traits<T>::kc + g * kPer + s;
+        for (int s = 0; s < 8; ++s) {
+            const int64_t ci = int64_t(chunk) * kc + g * 8 + s;
             vals[s] = (co < cout && ci < cin) ? w[(co * cin + ci) * taps + tap] : T(0);
         }
-        wfrag[e] = *reinterpret_cast<const uint4*>(vals);
+        uint4* dst = wfrag + (r * PT * nt + ntile) * 64 + lane;
+        if constexpr (PT == 1) {
+            *dst = *reinterpret_cast<const uint4*>(vals);
+        } else {
+            const bool neg = ((((tap % ptaps) * kcp + chunk % kcp) >> 1) & 1) != 0;
+            float f[8];
+#pragma unroll
+            for (int s = 0; s < 8; ++s) f[s] = neg ? -vals[s] : vals[s];
+            uint4 h, m, l;
+            split_bf16x3(f, h, m, l);
+            dst[0] = h;
+            dst[int64_t(nt) * 64] = m;
+            dst[int64_t(nt) * 128] = l;
+        }
     }
 }
 
+// The plan for waves of rm x rn tiles, wn waves along N. oext: the extent of the
+// outputs to compute (a region; default the whole box); like: a plan whose
+// channel passes and tap planes per pass to keep (a region's outputs are then
+// summed in the same order as in the whole box's plan: the order depends on the
+// passes, not on the tile shape).
 template <typename T>
-PlanF plan_fwd_t(const Tile3& t, const Conv3& cv, const int64_t* oext = nullptr, int64_t fix_cc = 0,
-                 int rm_over = 0)
+PlanF plan_fwd_cfg(const Tile3& t, const Conv3& cv, int rm, int rn, int wn, const int64_t* oext, const FwdArgs* like)
 {
-    // oext: the extent of the outputs to compute (a region; default the whole
-    // box); fix_cc: a channel pass width to keep (a region's outputs are then
-    // summed in the same order as in the whole box's plan: the order depends
-    // on the passes, not on the tile shape); rm_over: M tiles per wave
     PlanF pl{};
     const int64_t O[3] = {oext ? oext[0] : cv.O[0], oext ? oext[1] : cv.O[1], oext ? oext[2] : cv.O[2]};
-    constexpr int kc = Traits<T>::kc;
-    constexpr int esz = Traits<T>::esz;
+    constexpr bool f32 = std::is_same<T, float>::value;
+    constexpr int64_t chb = 2 * Traits<T>::parts;  // LDS bytes per channel
     const int64_t nt = ceil_div(cv.cout, 32);
-    int rn, rm;
-    if (std::is_same<T, bf16_t>::value) {
-        rn = nt >= 2 ? 2 : 1;
-        rm = rm_over == 2 && rn == 2 ? 2 : 4;
-    } else {
-        rn = nt >= 4 ? 4 : (nt >= 2 ? 2 : 1);
-        rm = rn == 4 ? 1 : (rn == 2 ? 2 : 4);
-    }
-    const int64_t cap = int64_t(kWaves) * rm * 32;
+    const int64_t cap = int64_t(kWaves / wn) * rm * 32;
     const int64_t cfull = round_up(t.c, kc);
     const size_t kLdsPref = 80 * 1024, kLdsMax = 160 * 1024;
+    const double taps = double(cv.taps());
 
     double best = 1e300;
     FwdArgs bestA{};
     size_t bestLds = 0;
-    auto consider = [&](int64_t b0, int64_t b1, int64_t b2) {
+    auto consider = [&](int64_t b0, int64_t b1, int64_t b2, int64_t kdp) {
         if (b0 < 1 || b1 < 1 || b2 < 1 || b0 * b1 * b2 > cap) return;
         int64_t bi[3], bo[3] = {b0, b1, b2};
         int64_t biv = 1;
         for (int k = 0; k < 3; ++k) {
             bi[k] = (bo[k] - 1) * cv.S[k] + cv.K[k];
+            if (k == 0 && kdp < cv.K[0]) bi[k] = bo[k];
             biv *= bi[k];
         }
         // channel pass width: the largest multiple of kc whose brick fits
         int64_t cc = cfull;
-        if (fix_cc > 0)
-            cc = fix_cc;
+        if (like)
+            cc = like->cc;
         else
-            while (cc > kc && size_t(biv * cc * esz) > kLdsPref) cc = round_up(cc / 2, kc);
-        size_t lds = size_t(biv * cc * esz);
+            while (cc > kc && size_t(biv * cc * chb) > kLdsPref) cc = round_up(cc / 2, kc);
+        // the brick, and at least the epilogue's tile per wave
+        const size_t lds = std::max(size_t(biv * cc * chb), size_t(kWaves) * 32 * 32 * Traits<T>::esz);
         if (lds > kLdsMax) return;
         double eff = double(b0 * b1 * b2) / double(cap);
         for (int k = 0; k < 3; ++k) {
             const int64_t nb = ceil_div(O[k], bo[k]);
             eff *= double(O[k]) / double(nb * bo[k]);
         }
-        double cost = double(biv) / double(b0 * b1 * b2) / eff;
+        // staged voxels per output; binary32 (where staging splits every value)
+        // weighs them against the products: SIMD cycles per output and 16 channels
+        const double ratio = double(biv) / double(b0 * b1 * b2) * double(cv.K[0] / kdp);
+        double cost = (f32 ? taps * 6.0 * rn * wn + 12.0 * ratio : ratio) / eff;
         if (lds > kLdsPref) cost *= 1.5;
-        cost *= 1.0 + 0.02 * double(ceil_div(cfull, cc) - 1);
+        cost *= 1.0 + 0.02 * double(ceil_div(cfull, cc) * (cv.K[0] / kdp) - 1);
         if (cost < best) {
             best = cost;
             bestLds = lds;
@@ -725,9 +838,10 @@ PlanF plan_fwd_t(const Tile3& t, const Conv3& cv, const int64_t* oext = nullptr,
             for (int k = 0; k < 3; ++k) {
                 a.BO[k] = int32_t(bo[k]);
                 a.BI[k] = int32_t(bi[k]);
-                a.NB[k] = int32_t(ceil_div(cv.O[k], bo[k]));
+                a.NB[k] = int32_t(ceil_div(O[k], bo[k]));
             }
             a.cc = int32_t(cc);
+            a.kdp = int32_t(kdp);
             bestA = a;
         }
     };
@@ -736,8 +850,15 @@ PlanF plan_fwd_t(const Tile3& t, const Conv3& cv, const int64_t* oext = nullptr,
         for (int64_t b1 = 1; b1 * w2 <= cap; b1 *= 2) {
             const int64_t w1 = std::min(b1, O[1]);
             const int64_t w0 = std::min(cap / (w1 * w2), O[0]);
-            consider(w0, w1, w2);
-            for (int64_t b0 = 1; b0 < w0; b0 *= 2) consider(b0, w1, w2);
+            auto depth = [&](int64_t kdp) {
+                if (like && like->kdp != kdp) return;
+                consider(w0, w1, w2, kdp);
+                for (int64_t b0 = 1; b0 < w0; b0 *= 2) consider(b0, w1, w2, kdp);
+            };
+            depth(cv.K[0]);
+            // one plane of taps per pass: a strided binary32 brick would not fit
+            // with all the planes that its taps meet
+            if (f32 && cv.K[0] > 1 && cv.S[0] > 1) depth(1);
         }
     }
     if (best >= 1e299) return pl;
@@ -752,19 +873,43 @@ PlanF plan_fwd_t(const Tile3& t, const Conv3& cv, const int64_t* oext = nullptr,
         a.S[k] = int32_t(cv.S[k]);
         a.pad[k] = int32_t(cv.pad[k]);
     }
-    a.nq = int32_t(a.cc * esz / 16);
+    a.nq = int32_t(a.cc / 8);
     a.npass = int32_t(ceil_div(cfull, a.cc));
     // fragment counts cover every index the kernel forms: npass * (cc / kc)
-    // K-chunks and ng * rn N tiles; the padding holds zero weights
+    // K-chunks and ng * wn * rn N tiles; the padding holds zero weights
     a.nkc = int32_t(int64_t(a.npass) * (a.cc / kc));
-    a.ng = int32_t(ceil_div(nt, rn));
-    a.nt = int32_t(int64_t(a.ng) * rn);
+    a.ng = int32_t(ceil_div(nt, rn * wn));
+    a.nt = int32_t(int64_t(a.ng) * rn * wn);
     a.nblocks = t.n * int64_t(a.NB[0]) * a.NB[1] * a.NB[2] * a.ng;
     pl.rm = rm;
     pl.rn = rn;
+    pl.wn = wn;
+    pl.cost = best;
     pl.a = a;
     pl.lds = bestLds;
     pl.ok = a.nblocks > 0 && a.nblocks < (int64_t(1) << 31);
+    return pl;
+}
+
+// The plan of the whole box, or (oext, like) of a region of it. Waves of four M
+// tiles (binary32: two) by two N tiles where there are two; binary32 puts two
+// waves along N from three N tiles on, so that a brick is staged and split once
+// for 128 output channels. rm_over: M tiles per wave.
+template <typename T>
+PlanF plan_fwd_t(const Tile3& t, const Conv3& cv, const int64_t* oext = nullptr, const FwdArgs* like = nullptr,
+                 int rm_over = 0)
+{
+    constexpr bool f32 = std::is_same<T, float>::value;
+    const int64_t nt = ceil_div(cv.cout, 32);
+    const int rn = nt >= 2 ? 2 : 1, wn = f32 && nt >= 3 ? 2 : 1;
+    const PlanF pl = plan_fwd_cfg<T>(t, cv, rm_over ? rm_over : (f32 ? 2 : 4), rn, wn, oext, like);
+    if (!f32 || rn != 1 || rm_over) return pl;
+    // one N tile: a brick of one M tile per wave where the larger one pays more
+    // than a tenth for its footprint (a strided 3D brick that leaves one
+    // workgroup per CU; 24 -> 16 channels, 3 x 3 x 3 at stride 2 over 210 x 290 x
+    // 316: 3.25 ms with two M tiles), or where it leaves CUs without a brick
+    const PlanF p1 = plan_fwd_cfg<T>(t, cv, 1, rn, wn, oext, like);
+    if (pl.ok && p1.ok && (p1.cost * 1.1 < pl.cost || pl.a.nblocks < 256)) return p1;
     return pl;
 }
 
@@ -782,15 +927,15 @@ size_t wfrag_bytes(const Tile3& t, const Conv3& cv)
 {
     const PlanF pl = plan_fwd_t<T>(t, cv);
     if (!pl.ok) return 0;
-    return size_t(cv.taps()) * size_t(pl.a.nkc) * size_t(pl.a.nt) * 64 * 16;
+    return size_t(cv.taps()) * size_t(pl.a.nkc) * size_t(pl.a.nt) * Traits<T>::parts * 64 * 16;
 }
 
 // n (1 to kMaxRegions) plans in one launch
-template <typename T, int RM, int RN>
+template <typename T, int RM, int RN, int WN>
 hipError_t launch_tiled(const PlanF* pl, int n, hipStream_t s)
 {
-    const void* fn = n > 1 ? reinterpret_cast<const void*>(&conv_fwd_tiledn<T, RM, RN>)
-                           : reinterpret_cast<const void*>(&conv_fwd_tiled<T, RM, RN>);
+    const void* fn = n > 1 ? reinterpret_cast<const void*>(&conv_fwd_tiledn<T, RM, RN, WN>)
+                           : reinterpret_cast<const void*>(&conv_fwd_tiled<T, RM, RN, WN>);
     size_t lds = 0;
     int64_t total = 0;
     for (int i = 0; i < n; ++i) {
@@ -823,12 +968,18 @@ hipError_t launch_tiled_plans(const PlanF* pl, int n, hipStream_t s)
 {
     if (n < 1 || n > kMaxRegions) return hipErrorInvalidValue;
     for (int i = 1; i < n; ++i)
-        if (pl[i].rm != pl[0].rm || pl[i].rn != pl[0].rn) return hipErrorNotSupported;
-    const int rm = pl[0].rm, rn = pl[0].rn;
-    if (rm == 4 && rn == 1) return launch_tiled<T, 4, 1>(pl, n, s);
-    if (rm == 4 && rn == 2) return launch_tiled<T, 4, 2>(pl, n, s);
-    if (rm == 2 && rn == 2) return launch_tiled<T, 2, 2>(pl, n, s);
-    if (rm == 1 && rn == 4) return launch_tiled<T, 1, 4>(pl, n, s);
+        if (pl[i].rm != pl[0].rm || pl[i].rn != pl[0].rn || pl[i].wn != pl[0].wn) return hipErrorNotSupported;
+    const int cfg = pl[0].rm * 100 + pl[0].rn * 10 + pl[0].wn;
+    if constexpr (std::is_same<T, bf16_t>::value) {
+        if (cfg == 411) return launch_tiled<T, 4, 1, 1>(pl, n, s);
+        if (cfg == 421) return launch_tiled<T, 4, 2, 1>(pl, n, s);
+        if (cfg == 221) return launch_tiled<T, 2, 2, 1>(pl, n, s);
+    } else {
+        if (cfg == 222) return launch_tiled<T, 2, 2, 2>(pl, n, s);
+        if (cfg == 221) return launch_tiled<T, 2, 2, 1>(pl, n, s);
+        if (cfg == 211) return launch_tiled<T, 2, 1, 1>(pl, n, s);
+        if (cfg == 111) return launch_tiled<T, 1, 1, 1>(pl, n, s);
+    }
     return hipErrorInvalidValue;
 }
 
@@ -871,16 +1022,16 @@ bool dense_map(const Conv3& cv, const OutMap& om)
 // region computes it.
 template <typename T>
 PlanF plan_region(const Tile3& t, const Conv3& cv, const void* tile, void* y, const OutMap& om, const Region& rg,
-                  const Fold* fold, void* ws)
+                  const Fold* fold, void* ws, int rm_over = 0)
 {
     PlanF pl = plan_fwd_t<T>(t, cv);
     if (!pl.ok) return pl;
     if (rg.ext[0] != cv.O[0] || rg.ext[1] != cv.O[1] || rg.ext[2] != cv.O[2]) {
         auto same_passes = [&](const PlanF& q) {
-            return q.ok && q.rn == pl.rn && q.a.cc == pl.a.cc && q.a.npass == pl.a.npass && q.a.nkc == pl.a.nkc &&
-                   q.a.nt == pl.a.nt;
+            return q.ok && q.rn == pl.rn && q.wn == pl.wn && q.a.cc == pl.a.cc && q.a.kdp == pl.a.kdp &&
+                   q.a.npass == pl.a.npass && q.a.nkc == pl.a.nkc && q.a.nt == pl.a.nt;
         };
-        PlanF pr = plan_fwd_t<T>(t, cv, rg.ext, pl.a.cc);
+        PlanF pr = plan_fwd_t<T>(t, cv, rg.ext, &pl.a, rm_over);
         // a thin region with fewer bricks than the 512 resident workgroups
         // takes half-height bricks (two M tiles per wave) where that exists
         auto region_blocks = [&](const PlanF& q) {
@@ -888,7 +1039,7 @@ PlanF plan_region(const Tile3& t, const Conv3& cv, const void* tile, void* y, co
                    ceil_div(rg.ext[2], q.a.BO[2]) * q.a.ng;
         };
         if (same_passes(pr) && pr.rm == 4 && pr.rn == 2 && region_blocks(pr) < 512) {
-            const PlanF p2 = plan_fwd_t<T>(t, cv, rg.ext, pl.a.cc, 2);
+            const PlanF p2 = plan_fwd_t<T>(t, cv, rg.ext, &pl.a, 2);
             if (same_passes(p2) && p2.rm == 2) pr = p2;
         }
         if (same_passes(pr)) pl = pr;
@@ -927,7 +1078,7 @@ hipError_t lay_wfrag(const Tile3& t, const Conv3& cv, const PlanF& pl, const voi
     const int64_t frag_total = int64_t(taps) * pl.a.nkc * pl.a.nt * 64;
     const unsigned fg = unsigned(std::max<int64_t>(1, std::min<int64_t>(ceil_div(frag_total, 256), 4096)));
     hipLaunchKernelGGL(wfrag_kernel<T>, dim3(fg), dim3(256), 0, s, static_cast<const T*>(w), static_cast<uint4*>(ws),
-                       t.c, cv.cout, taps, pl.a.nkc, pl.a.nt);
+                       t.c, cv.cout, taps, pl.a.nkc, pl.a.nt, int(pl.a.kdp * cv.K[1] * cv.K[2]), pl.a.cc / kc);
     return hipGetLastError();
 }
 
@@ -957,11 +1108,21 @@ hipError_t run_fwd_group(const Tile3& t, const Conv3& cv, const void* tile, cons
     if (n < 2 || n > kMaxRegions) return hipErrorNotSupported;
     PlanF pl[kMaxRegions];
     int64_t total = 0;
-    for (int i = 0; i < n; ++i) {
-        pl[i] = plan_region<T>(t, cv, tile, y, om, rs[i], fold, ws);
-        if (!pl[i].ok) return hipErrorInvalidValue;
-        if (pl[i].rm != pl[0].rm || pl[i].rn != pl[0].rn) return hipErrorNotSupported;
-        total += pl[i].a.nblocks;
+    // every region with the fewest M tiles per wave that one of them asks for
+    int rm = 0;
+    for (int pass = 0; pass < 2; ++pass) {
+        bool same = true;
+        total = 0;
+        for (int i = 0; i < n; ++i) {
+            if (pass == 0 || pl[i].rm != rm) pl[i] = plan_region<T>(t, cv, tile, y, om, rs[i], fold, ws, rm);
+            if (!pl[i].ok) return hipErrorInvalidValue;
+            same = same && pl[i].rm == pl[0].rm && pl[i].rn == pl[0].rn && pl[i].wn == pl[0].wn;
+            total += pl[i].a.nblocks;
+        }
+        if (same) break;
+        if (pass == 1) return hipErrorNotSupported;
+        rm = pl[0].rm;
+        for (int i = 1; i < n; ++i) rm = std::min(rm, pl[i].rm);
     }
     if (total >= (int64_t(1) << 31)) return hipErrorNotSupported;
     if (!frags_ready) {
@@ -1034,7 +1195,7 @@ hipError_t launch_conv_fwd_region_pair(const Tile3& t, const Conv3& cv, shard_dt
         const int64_t frag_total = int64_t(taps) * pl.a.nkc * pl.a.nt * 64;
         const unsigned fg = unsigned(std::max<int64_t>(1, std::min<int64_t>(ceil_div(frag_total, 256), 4096)));
         hipLaunchKernelGGL(wfrag_kernel<bf16_t>, dim3(fg), dim3(256), 0, s, static_cast<const bf16_t*>(w),
-                           static_cast<uint4*>(ws), t.c, cv.cout, taps, pl.a.nkc, pl.a.nt);
+                           static_cast<uint4*>(ws), t.c, cv.cout, taps, pl.a.nkc, pl.a.nt, taps, pl.a.nkc);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -147,9 +147,9 @@ hipError_t launch_conv_fwd_tiled_group(const Tile3& t, const Conv3& cv, shard_dt
                                        const void* w, void* y, const OutMap& om, const Region* rs, int n,
                                        const Fold* fold, void* ws, hipStream_t s, bool frags_ready);
 // The forward with its workspace in the library's per-device scratch array
-// (noalloc.hip): bytes it holds, and the launch (the caller has checked that
-// conv_fwd_workspace fits).
-size_t conv_fwd_noalloc_limit();
+// (noalloc.hip): whether the workspace fits it, and the launch (the caller has
+// checked that).
+bool conv_fwd_noalloc_fits(const Tile3& t, const Conv3& cv, shard_dtype_t dt);
 hipError_t launch_conv_fwd_noalloc(const Tile3& t, const Conv3& cv, shard_dtype_t dt, const void* tile,
                                    const void* w, void* y, hipStream_t s);
 hipError_t launch_conv_wgrad(const Tile3& t, const Conv3& cv, shard_dtype_t dt, const void* tile, const void* dy,

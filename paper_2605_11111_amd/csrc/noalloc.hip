@@ -9,10 +9,12 @@
 namespace shardconv {
 namespace {
 
-// Upper bound of the weight-fragment scratch: 4 MiB holds the fragments of
-// every workload shape of this library (the largest, 64 -> 128 channels at
-// 3 x 3 x 3 in binary32, needs 864 KiB).
-constexpr size_t kScratchBytes = size_t(4) << 20;
+// Upper bound of the weights in fragment order, one binary32 or bf16 value each:
+// 4 MiB holds every workload shape of this library (the largest, 64 -> 128
+// channels at 3 x 3 x 3 in binary32, has 864 KiB). The scratch holds binary32
+// fragments as three bf16 parts, of channels rounded up to 16.
+constexpr size_t kWeightBytes = size_t(4) << 20;
+constexpr size_t kScratchBytes = size_t(16) << 20;
 
 __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -42,7 +44,16 @@ hipError_t scratch_ptr(void** out)
 
 }  // namespace
 
-size_t conv_fwd_noalloc_limit() { return kScratchBytes; }
+bool conv_fwd_noalloc_fits(const Tile3& t, const Conv3& cv, shard_dtype_t dt)
+{
+    // the weights as single fragments, in channels rounded to 8 (binary32) or as
+    // the plan lays them out (bf16), within 4 MiB; binary32 fragments hold three
+    // bf16 parts of channels rounded to 16, at most three times that plus a pass's rounding
+    const size_t ws = conv_fwd_workspace(t, cv, dt);
+    if (dt == SHARD_BF16) return ws <= kWeightBytes;
+    const int64_t nt = ceil_div(cv.cout, 32), ntr = nt >= 3 ? round_up(nt, 4) : nt;
+    return size_t(cv.taps() * ceil_div(t.c, 8) * ntr) * 1024 <= kWeightBytes && ws <= kScratchBytes;
+}
 
 hipError_t launch_conv_fwd_noalloc(const Tile3& t, const Conv3& cv, shard_dtype_t dt, const void* tile,
                                    const void* w, void* y, hipStream_t s)

@@ -652,7 +652,7 @@ def time_group_norm(sc, w, g, desc, tile, args, stream):
 # itself, its host-side launcher and the shared headers.
 KERNEL_SOURCES = {
     "conv_fwd": ["conv_fwd.hip", "conv_fwd_rows.hip", "common.h", "internal.h"],
-    "conv_wgrad": ["conv_wgrad.hip", "conv_wgrad_xm.hip", "common.h", "internal.h"],
+    "conv_wgrad": ["conv_wgrad.hip", "conv_wgrad_xm.hip", "conv_wgrad_any.hip", "common.h", "internal.h"],
     "halo": ["halo.hip", "common.h", "internal.h"],
 }
 

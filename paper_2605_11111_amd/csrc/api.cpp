@@ -758,10 +758,10 @@ shard_status_t shard_norm_stats(const shard_tile_t* x, shard_dtype_t dtype, cons
     Tile3 t;
     if (!norm_tile(x, dtype, t) || groups < 1 || groups > t.c || t.c % groups != 0) return SHARD_ERR_INVALID;
     if (t.n == 0) return SHARD_OK;
-    const size_t need = norm_workspace(t, groups);
+    const size_t need = norm_workspace_least(t, groups);
     if (!sums || !ws || ws_bytes < need || !aligned(sums, 8) || !aligned(ws, 16)) return SHARD_ERR_INVALID;
     if (tile_elems(t) > 0 && (!tile || !aligned(tile, t.esz))) return SHARD_ERR_INVALID;
-    return map_hip(launch_norm_stats(t, dtype, tile, groups, sums, ws, stream));
+    return map_hip(launch_norm_stats(t, dtype, tile, groups, sums, ws, ws_bytes, stream));
 }
 
 shard_status_t shard_norm_apply(const shard_tile_t* x, shard_dtype_t dtype, const void* tile, const double* sums,
@@ -772,7 +772,7 @@ shard_status_t shard_norm_apply(const shard_tile_t* x, shard_dtype_t dtype, cons
     if (!norm_tile(x, dtype, t) || groups < 1 || groups > t.c || t.c % groups != 0) return SHARD_ERR_INVALID;
     if (!(count > 0.0) || !(count < 1e300) || !(eps >= 0.0) || !(eps < 1e300)) return SHARD_ERR_INVALID;
     if (t.n * t.ext[0] * t.ext[1] * t.ext[2] == 0) return SHARD_OK;
-    const size_t need = norm_workspace(t, groups);
+    const size_t need = norm_workspace_least(t, groups);
     if (!tile || !out || !sums || !gamma || !beta || !ws || ws_bytes < need) return SHARD_ERR_INVALID;
     if (!aligned(tile, t.esz) || !aligned(out, t.esz) || !aligned(sums, 8) || !aligned(gamma, 4) ||
         !aligned(beta, 4) || !aligned(ws, 16))

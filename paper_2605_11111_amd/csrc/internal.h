@@ -164,8 +164,9 @@ hipError_t launch_conv_dgrad(const Tile3& t, const Conv3& cv, shard_dtype_t dt, 
 
 // Group normalisation of a shard's interior (see norm.hip).
 size_t norm_workspace(const Tile3& t, int64_t groups);
+size_t norm_workspace_least(const Tile3& t, int64_t groups);
 hipError_t launch_norm_stats(const Tile3& t, shard_dtype_t dt, const void* tile, int64_t groups, double* sums,
-                             void* ws, hipStream_t s);
+                             void* ws, size_t ws_bytes, hipStream_t s);
 hipError_t launch_norm_apply(const Tile3& t, shard_dtype_t dt, const void* tile, const double* sums, double count,
                              double eps, int64_t groups, const float* gamma, const float* beta, void* out, void* ws,
                              hipStream_t s);

@@ -9,12 +9,15 @@
 // Both passes stream the interior once (HBM-bound), with nontemporal loads: the
 // tile is read once per pass, and streaming it past the caches took 27 % less
 // time for the statistics pass and 7 % less for the normalisation on a 2 GiB
-// interior. The interior is a set of
-// W runs of ext2 * C contiguous elements. On the vector path (C * esz a
-// multiple of 16, 16-byte aligned tile, 256 vectors span whole channel sets) a
-// thread reads 16-byte vectors whose channels never change, so it keeps its
-// channels' sums, scales and shifts in registers; other shapes take an
-// element-wise path.
+// interior. On the vector path (C * esz a multiple of 16, at most kT vectors a
+// voxel, 16-byte aligned tile) the interior is one sequence of 16-byte vectors:
+// axes without margins are merged, a block takes a range of voxels wherever the
+// rows end, and a thread steps by a whole number of voxels, so that its channels
+// never change and it keeps their sums, scales and shifts in registers. Blocks
+// that took whole rows left lanes idle at each row's end (628 vectors a row: 39 %
+// of the loads in flight) and were too few where rows are few: 48 x 131 x 157
+// x 32 in bf16, both calls, 59.0 us -> 50.2 us together with the changes to
+// norm_stats_final and the scales below. Other shapes take an element-wise path.
 //
 // Statistics: pass 1 gives every block (a fixed range of rows of one batch
 // item) fp32 per-channel sums of the values shifted by a pivot (the channel's
@@ -33,6 +36,7 @@ namespace shardconv {
 namespace {
 
 constexpr int kT = 256;
+constexpr int kF = 1024;  // threads of a norm_stats_final block
 constexpr int kU = 4;  // 16-byte loads in flight per thread
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_n;
 
@@ -47,7 +51,12 @@ struct NormArgs {
     int64_t n, c, G;
     int64_t P[3], lo[3], ext[3];
     int64_t rows;           // interior rows per batch item: ext0 * ext1
-    int64_t B;              // stats blocks per batch item
+    int64_t B;              // blocks per batch item
+    int64_t units, unit;    // stats: what the blocks divide (voxels, or rows of `unit` voxels)
+    // vector path, in 16-byte vectors: a voxel, the threads that work, an interior row and a
+    // row of the tile, a batch item; a step of `active` vectors (see Walk)
+    int64_t per, active, nvec, line, item;
+    int64_t step, step_v, step_1, carry_v, carry_1;
     double count, eps;
 };
 
@@ -62,59 +71,97 @@ struct Vec16 {
     static constexpr int N = 16 / int(sizeof(T));
 };
 
-// pass 1, vector path: block (nn, b) sums rows [b * rows / B, (b + 1) * rows / B)
+// first of block b's share of `units`, which differ by one at most
+__device__ __forceinline__ int64_t share(int64_t units, int64_t B, int64_t b)
+{
+    const int64_t q = units / B, r = units % B;
+    return b * q + (b < r ? b : r);
+}
+
+// A thread's place in the interior's sequence of vectors: the vector within its row,
+// the row within its plane, and the vector's index in the tile. A step adds constants
+// and two carries, so the rows' ends cost no division.
+struct Walk {
+    int64_t v, i1, off;
+    __device__ __forceinline__ Walk(const NormArgs& a, int64_t nn, int64_t f)
+    {
+        v = f % a.nvec;
+        const int64_t row = f / a.nvec;
+        i1 = row % a.ext[1];
+        off = nn * a.item + ((a.lo[0] + row / a.ext[1]) * a.P[1] + a.lo[1] + i1) * a.line + a.lo[2] * a.per + v;
+    }
+    __device__ __forceinline__ void next(const NormArgs& a)
+    {
+        off += a.step;
+        v += a.step_v;
+        i1 += a.step_1;
+        if (v >= a.nvec) {
+            v -= a.nvec;
+            off += a.carry_v;
+            ++i1;
+        }
+        if (i1 >= a.ext[1]) {
+            i1 -= a.ext[1];
+            off += a.carry_1;
+        }
+    }
+};
+
+__device__ __forceinline__ uint4 load_nt(const u32x4_n* p)
+{
+    const u32x4_n t = __builtin_nontemporal_load(p);
+    return make_uint4(t[0], t[1], t[2], t[3]);
+}
+
+// pass 1, vector path: block (nn, b) sums its share of the voxels
 template <typename T>
 __global__ __launch_bounds__(kT) void norm_stats_vec(NormArgs a)
 {
     constexpr int VE = Vec16<T>::N;
     __shared__ float red[2][kT][VE];
     const int64_t nn = blockIdx.x / a.B, b = blockIdx.x % a.B;
-    const int64_t r0 = b * a.rows / a.B, r1 = (b + 1) * a.rows / a.B;
-    const int64_t nvec = a.ext[2] * a.c / VE;
+    const int64_t f0 = share(a.units, a.B, b) * a.per, f1 = share(a.units, a.B, b + 1) * a.per;
+    const u32x4_n* src = reinterpret_cast<const u32x4_n*>(a.x);
     const int tid = threadIdx.x;
-    // pivot: the block's first voxel, the thread's channels (a thread's vectors
-    // always hold the same channels)
-    const int per = int(a.c / VE);
-    float piv[VE];
-    {
-        uint4 u0 = make_uint4(0u, 0u, 0u, 0u);
-        if (r0 < r1)
-            u0 = reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(a.x) + run_offset(a, nn, r0))[tid % per];
+    const int per = int(a.per), active = int(a.active);
+    float piv[VE], s1[VE], s2[VE];
+#pragma unroll
+    for (int i = 0; i < VE; ++i) piv[i] = s1[i] = s2[i] = 0.f;
+    auto add = [&](const uint4& u) {
         T e[VE];
-        __builtin_memcpy(e, &u0, 16);
+        __builtin_memcpy(e, &u, 16);
 #pragma unroll
-        for (int i = 0; i < VE; ++i) piv[i] = to_f32(e[i]);
-    }
-    float s1[VE], s2[VE];
+        for (int i = 0; i < VE; ++i) {
+            const float f = to_f32(e[i]) - piv[i];
+            s1[i] += f;
+            s2[i] = fmaf(f, f, s2[i]);
+        }
+    };
+    if (tid < active && f0 < f1) {
+        // pivot: the block's first voxel, the thread's channels
+        {
+            const uint4 u0 = load_nt(src + Walk(a, nn, f0 + tid % per).off);
+            T e[VE];
+            __builtin_memcpy(e, &u0, 16);
 #pragma unroll
-    for (int i = 0; i < VE; ++i) s1[i] = s2[i] = 0.f;
-    for (int64_t row = r0; row < r1; ++row) {
-        const uint4* src = reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(a.x) + run_offset(a, nn, row));
+            for (int i = 0; i < VE; ++i) piv[i] = to_f32(e[i]);
+        }
+        int64_t f = f0 + tid;
+        Walk w(a, nn, f);
         // kU loads in flight per thread before the arithmetic
-        for (int64_t v0 = tid; v0 < nvec; v0 += kU * kT) {
+        for (; f + (kU - 1) * active < f1; f += kU * active) {
             uint4 u[kU];
 #pragma unroll
             for (int j = 0; j < kU; ++j) {
-                const int64_t v = v0 + j * kT;
-                if (v < nvec) {
-                    const u32x4_n t = __builtin_nontemporal_load(reinterpret_cast<const u32x4_n*>(src) + v);
-                    u[j] = make_uint4(t[0], t[1], t[2], t[3]);
-                } else {
-                    u[j] = make_uint4(0u, 0u, 0u, 0u);
-                }
+                u[j] = load_nt(src + w.off);
+                w.next(a);
             }
 #pragma unroll
-            for (int j = 0; j < kU; ++j) {
-                T e[VE];
-                __builtin_memcpy(e, &u[j], 16);
-#pragma unroll
-                for (int i = 0; i < VE; ++i) {
-                    // a vector past the row end holds zeros: it adds nothing
-                    const float f = v0 + j * kT < nvec ? to_f32(e[i]) - piv[i] : 0.f;
-                    s1[i] += f;
-                    s2[i] = fmaf(f, f, s2[i]);
-                }
-            }
+            for (int j = 0; j < kU; ++j) add(u[j]);
+        }
+        for (; f < f1; f += active) {
+            add(load_nt(src + w.off));
+            w.next(a);
         }
     }
 #pragma unroll
@@ -123,16 +170,18 @@ __global__ __launch_bounds__(kT) void norm_stats_vec(NormArgs a)
         red[1][tid][i] = s2[i];
     }
     __syncthreads();
-    // threads tid and tid + k * (C / VE) hold the same channels: fold in a fixed tree
-    for (int step = kT / 2; step >= per; step /= 2) {
-        if (tid < step) {
+    // threads tid and tid + k * per hold the same channels: fold in a fixed tree
+    for (int m = active / per; m > 1;) {
+        const int half = (m + 1) / 2;
+        if (tid < (m - half) * per) {
 #pragma unroll
             for (int i = 0; i < VE; ++i) {
-                red[0][tid][i] += red[0][tid + step][i];
-                red[1][tid][i] += red[1][tid + step][i];
+                red[0][tid][i] += red[0][tid + half * per][i];
+                red[1][tid][i] += red[1][tid + half * per][i];
             }
         }
         __syncthreads();
+        m = half;
     }
     if (tid < per) {
         float* out = a.part + (nn * a.B + b) * a.c * 3;
@@ -151,7 +200,7 @@ template <typename T>
 __global__ __launch_bounds__(kT) void norm_stats_elem(NormArgs a)
 {
     const int64_t nn = blockIdx.x / a.B, b = blockIdx.x % a.B;
-    const int64_t r0 = b * a.rows / a.B, r1 = (b + 1) * a.rows / a.B;
+    const int64_t r0 = share(a.rows, a.B, b), r1 = share(a.rows, a.B, b + 1);
     const int64_t run = a.ext[2] * a.c;
     float* out = a.part + (nn * a.B + b) * a.c * 3;
     for (int64_t ch = threadIdx.x; ch < a.c; ch += kT) {
@@ -171,27 +220,38 @@ __global__ __launch_bounds__(kT) void norm_stats_elem(NormArgs a)
     }
 }
 
-// pass 2: block (nn, g) adds the B blocks' sums of the group's channels in float64
-__global__ __launch_bounds__(kT) void norm_stats_final(NormArgs a)
+// pass 2: block (nn, g) adds the B blocks' sums of the group's channels in float64.
+// A chain of loads and divisions bounds it: 1024 threads take a quarter of the trips
+// of 256, and a step adds a constant instead of dividing (21 us -> 6.5 us for the
+// 1024 blocks of 32 channels in 4 groups).
+__global__ __launch_bounds__(kF) void norm_stats_final(NormArgs a)
 {
-    __shared__ double red[2][kT];
+    __shared__ double red[2][kF];
     const int64_t nn = blockIdx.x / a.G, g = blockIdx.x % a.G;
     const int64_t cpg = a.c / a.G;
-    const int64_t items = a.B * cpg;
+    const int64_t db = kF / cpg, dch = kF % cpg;
+    const int64_t q = a.units / a.B, r = a.units % a.B;
     double s1 = 0.0, s2 = 0.0;
-    for (int64_t k = threadIdx.x; k < items; k += kT) {
-        const int64_t b = k / cpg, ch = g * cpg + k % cpg;
-        const float* p = a.part + ((nn * a.B + b) * a.c + ch) * 3;
+    int64_t b = threadIdx.x / cpg, ch = threadIdx.x % cpg;
+#pragma unroll 4
+    while (b < a.B) {
+        const float* p = a.part + ((nn * a.B + b) * a.c + g * cpg + ch) * 3;
         // voxels of block b per channel
-        const double cnt = double((b + 1) * a.rows / a.B - b * a.rows / a.B) * double(a.ext[2]);
+        const double cnt = double(q + (b < r ? 1 : 0)) * double(a.unit);
         const double d1 = double(p[0]), d2 = double(p[1]), piv = double(p[2]);
         s1 += d1 + cnt * piv;
         s2 += d2 + (2.0 * piv) * d1 + cnt * piv * piv;
+        b += db;
+        ch += dch;
+        if (ch >= cpg) {
+            ch -= cpg;
+            ++b;
+        }
     }
     red[0][threadIdx.x] = s1;
     red[1][threadIdx.x] = s2;
     __syncthreads();
-    for (int step = kT / 2; step >= 1; step /= 2) {
+    for (int step = kF / 2; step >= 1; step /= 2) {
         if (int(threadIdx.x) < step) {
             red[0][threadIdx.x] += red[0][threadIdx.x + step];
             red[1][threadIdx.x] += red[1][threadIdx.x + step];
@@ -204,68 +264,80 @@ __global__ __launch_bounds__(kT) void norm_stats_final(NormArgs a)
     }
 }
 
-// scale[n][c] = gamma[c] * rstd[n][g], shift[n][c] = beta[c] - mean[n][g] * scale, from
-// the totals over all shards (float64, rounded once to binary32)
+// scale = gamma[c] * rstd[n][g], shift = beta[c] - mean[n][g] * scale, from the totals over
+// all shards (float64, rounded once to binary32)
+__device__ __forceinline__ float2 affine_of(const NormArgs& a, int64_t nn, int64_t ch)
+{
+    const int64_t g = ch / (a.c / a.G);
+    const double mean = a.sums[(nn * a.G + g) * 2] / a.count;
+    const double var = fmax(a.sums[(nn * a.G + g) * 2 + 1] / a.count - mean * mean, 0.0);
+    const double rstd = 1.0 / sqrt(var + a.eps);
+    const double sc = double(a.gamma[ch]) * rstd;
+    return make_float2(float(sc), float(double(a.beta[ch]) - mean * sc));
+}
+
+// the element path's scales and shifts, [n][c][2]
 __global__ __launch_bounds__(kT) void norm_affine(NormArgs a)
 {
     const int64_t total = a.n * a.c;
     for (int64_t e = int64_t(blockIdx.x) * kT + threadIdx.x; e < total; e += int64_t(gridDim.x) * kT) {
-        const int64_t nn = e / a.c, ch = e % a.c, g = ch / (a.c / a.G);
-        const double mean = a.sums[(nn * a.G + g) * 2] / a.count;
-        const double var = fmax(a.sums[(nn * a.G + g) * 2 + 1] / a.count - mean * mean, 0.0);
-        const double rstd = 1.0 / sqrt(var + a.eps);
-        const double sc = double(a.gamma[ch]) * rstd;
-        a.part[e * 2] = float(sc);
-        a.part[e * 2 + 1] = float(double(a.beta[ch]) - mean * sc);
+        const float2 f = affine_of(a, e / a.c, e % a.c);
+        a.part[e * 2] = f.x;
+        a.part[e * 2 + 1] = f.y;
     }
 }
 
+// every block works the scales and shifts out for itself, one channel a thread, while the
+// chip fills: a launch of its own for them took 4.1 us; the pass over 2 GiB takes
+// 811 us with them, 822 us before
 template <typename T>
 __global__ __launch_bounds__(kT) void norm_apply_vec(NormArgs a)
 {
     constexpr int VE = Vec16<T>::N;
-    const int64_t nvec = a.ext[2] * a.c / VE;
-    const int per = int(a.c / VE);
+    __shared__ float2 aff[kT * VE];
     const int tid = threadIdx.x;
-    const int cb = (tid % per) * VE;  // first channel of this thread's vectors
-    // grid: blockIdx.x runs over (n, row chunk)
-    const int64_t chunks = gridDim.x / a.n;
-    const int64_t nn = blockIdx.x / chunks, b = blockIdx.x % chunks;
-    const int64_t r0 = b * a.rows / chunks, r1 = (b + 1) * a.rows / chunks;
+    const int per = int(a.per), active = int(a.active);
+    const int64_t nn = blockIdx.x / a.B, b = blockIdx.x % a.B;
+    const int64_t f0 = share(a.units, a.B, b) * a.per, f1 = share(a.units, a.B, b + 1) * a.per;
+    for (int ch = tid; ch < int(a.c); ch += kT) aff[ch] = affine_of(a, nn, ch);
+    __syncthreads();
+    if (tid >= active || f0 >= f1) return;
     float sc[VE], sh[VE];
 #pragma unroll
     for (int i = 0; i < VE; ++i) {
-        sc[i] = a.part[(nn * a.c + cb + i) * 2];
-        sh[i] = a.part[(nn * a.c + cb + i) * 2 + 1];
+        const float2 f = aff[(tid % per) * VE + i];
+        sc[i] = f.x;
+        sh[i] = f.y;
     }
-    for (int64_t row = r0; row < r1; ++row) {
-        const int64_t off = run_offset(a, nn, row);
-        const uint4* src = reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(a.x) + off);
-        u32x4_n* dst = reinterpret_cast<u32x4_n*>(reinterpret_cast<T*>(a.y) + off);
-        for (int64_t v0 = tid; v0 < nvec; v0 += kU * kT) {
-            uint4 u[kU];
+    const u32x4_n* src = reinterpret_cast<const u32x4_n*>(a.x);
+    u32x4_n* dst = reinterpret_cast<u32x4_n*>(a.y);
+    auto put = [&](const uint4& u, int64_t off) {
+        T e[VE];
+        __builtin_memcpy(e, &u, 16);
 #pragma unroll
-            for (int j = 0; j < kU; ++j) {
-                const int64_t v = v0 + j * kT;
-                if (v < nvec) {
-                    const u32x4_n t = __builtin_nontemporal_load(reinterpret_cast<const u32x4_n*>(src) + v);
-                    u[j] = make_uint4(t[0], t[1], t[2], t[3]);
-                }
-            }
+        for (int i = 0; i < VE; ++i) e[i] = from_f32<T>(fmaf(to_f32(e[i]), sc[i], sh[i]));
+        u32x4_n r;
+        __builtin_memcpy(&r, e, 16);
+        // the normalised tile is consumed by the next layer, not by this kernel
+        __builtin_nontemporal_store(r, dst + off);
+    };
+    int64_t f = f0 + tid;
+    Walk w(a, nn, f);
+    for (; f + (kU - 1) * active < f1; f += kU * active) {
+        uint4 u[kU];
+        int64_t off[kU];
 #pragma unroll
-            for (int j = 0; j < kU; ++j) {
-                const int64_t v = v0 + j * kT;
-                if (v >= nvec) continue;
-                T e[VE];
-                __builtin_memcpy(e, &u[j], 16);
-#pragma unroll
-                for (int i = 0; i < VE; ++i) e[i] = from_f32<T>(fmaf(to_f32(e[i]), sc[i], sh[i]));
-                u32x4_n r;
-                __builtin_memcpy(&r, e, 16);
-                // the normalised tile is consumed by the next layer, not by this kernel
-                __builtin_nontemporal_store(r, dst + v);
-            }
+        for (int j = 0; j < kU; ++j) {
+            off[j] = w.off;
+            u[j] = load_nt(src + w.off);
+            w.next(a);
         }
+#pragma unroll
+        for (int j = 0; j < kU; ++j) put(u[j], off[j]);
+    }
+    for (; f < f1; f += active) {
+        put(load_nt(src + w.off), w.off);
+        w.next(a);
     }
 }
 
@@ -297,17 +369,58 @@ NormArgs make_norm(const Tile3& t, int64_t groups)
         a.ext[k] = t.ext[k];
     }
     a.rows = t.ext[0] * t.ext[1];
-    // about 1024 stats blocks in all, at most one per row
-    a.B = std::max<int64_t>(1, std::min<int64_t>(a.rows, ceil_div(1024, std::max<int64_t>(t.n, 1))));
     return a;
 }
 
 bool vec_path(const Tile3& t, const void* x, const void* y)
 {
-    const int64_t ve = 16 / t.esz;
-    return (t.c * t.esz) % 16 == 0 && (int64_t(kT) * ve) % t.c == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
+    return (t.c * t.esz) % 16 == 0 && t.c * t.esz <= 16 * kT && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
            (y == nullptr || reinterpret_cast<uintptr_t>(y) % 16 == 0);
 }
+
+// element path: about `blocks` blocks in all, at most one per row
+void plan_rows(NormArgs& a, int64_t blocks)
+{
+    a.B = std::max<int64_t>(1, std::min<int64_t>(a.rows, ceil_div(blocks, std::max<int64_t>(a.n, 1))));
+    a.units = a.rows;
+    a.unit = a.ext[2];
+}
+
+// vector path: about `blocks` blocks in all, each with a vector per thread at least
+void plan_vectors(NormArgs& a, int64_t esz, int64_t blocks)
+{
+    // axes without margins join the next outer one
+    for (int k = 0; k < 2 && a.ext[2] == a.P[2]; ++k) {
+        a.ext[2] *= a.ext[1];
+        a.lo[2] = a.lo[1] * a.P[2];
+        a.P[2] *= a.P[1];
+        a.ext[1] = a.ext[0];
+        a.lo[1] = a.lo[0];
+        a.P[1] = a.P[0];
+        a.ext[0] = a.P[0] = 1;
+        a.lo[0] = 0;
+    }
+    a.rows = a.ext[0] * a.ext[1];
+    a.units = a.rows * a.ext[2];
+    a.unit = 1;
+    a.per = a.c * esz / 16;
+    a.active = kT / a.per * a.per;
+    a.nvec = a.ext[2] * a.per;
+    a.line = a.P[2] * a.per;
+    a.item = a.P[0] * a.P[1] * a.line;
+    const int64_t nvec = std::max<int64_t>(a.nvec, 1), ext1 = std::max<int64_t>(a.ext[1], 1);
+    const int64_t rows = a.active / nvec;
+    a.step_v = a.active % nvec;
+    a.step_1 = rows % ext1;
+    a.step = (rows / ext1 * a.P[1] + a.step_1) * a.line + a.step_v;
+    a.carry_v = a.line - a.nvec;
+    a.carry_1 = (a.P[1] - a.ext[1]) * a.line;
+    a.B = std::max<int64_t>(1, std::min<int64_t>(a.units * a.per / kT, ceil_div(blocks, std::max<int64_t>(a.n, 1))));
+}
+
+// stats blocks in all: the second pass reads their sums, so more cost it time
+constexpr int64_t kStatsBlocks = 1024;
+constexpr int64_t kApplyBlocks = 2048;
 
 unsigned grid_of(int64_t total) { return unsigned(std::max<int64_t>(1, std::min<int64_t>(ceil_div(total, kT), 1 << 16))); }
 
@@ -315,20 +428,43 @@ unsigned grid_of(int64_t total) { return unsigned(std::max<int64_t>(1, std::min<
 
 size_t norm_workspace(const Tile3& t, int64_t groups)
 {
-    const NormArgs a = make_norm(t, groups);
-    return size_t(std::max(a.n * a.B * a.c * 3, a.n * a.c * 2)) * sizeof(float);
+    // either path: the tile's address, which may rule the vectors out, is not known here
+    NormArgs a = make_norm(t, groups);
+    plan_rows(a, kStatsBlocks);
+    int64_t B = a.B;
+    if (vec_path(t, nullptr, nullptr)) {
+        plan_vectors(a, t.esz, kStatsBlocks);
+        B = std::max(B, a.B);
+    }
+    return size_t(std::max(t.n * B * t.c * 3, t.n * t.c * 2)) * sizeof(float);
+}
+
+// what a call needs at least: the element path's blocks. Between the two the vector path
+// takes as many blocks as the workspace holds.
+size_t norm_workspace_least(const Tile3& t, int64_t groups)
+{
+    NormArgs a = make_norm(t, groups);
+    plan_rows(a, kStatsBlocks);
+    return size_t(std::max(t.n * a.B * t.c * 3, t.n * t.c * 2)) * sizeof(float);
 }
 
 hipError_t launch_norm_stats(const Tile3& t, shard_dtype_t dt, const void* tile, int64_t groups, double* sums,
-                             void* ws, hipStream_t s)
+                             void* ws, size_t ws_bytes, hipStream_t s)
 {
     NormArgs a = make_norm(t, groups);
     a.x = static_cast<const char*>(tile);
     a.part = static_cast<float*>(ws);
     a.out = sums;
     void* args[] = {&a};
-    const unsigned blocks = unsigned(a.n * a.B);
     const bool vec = vec_path(t, tile, nullptr);
+    if (vec) {
+        plan_vectors(a, t.esz, kStatsBlocks);
+        // never below one: a call brings norm_workspace_least() bytes
+        a.B = std::min<int64_t>(a.B, int64_t(ws_bytes / (size_t(a.n) * size_t(a.c) * 3 * sizeof(float))));
+    } else {
+        plan_rows(a, kStatsBlocks);
+    }
+    const unsigned blocks = unsigned(a.n * a.B);
     const void* fn;
     if (dt == SHARD_BF16)
         fn = vec ? reinterpret_cast<const void*>(&norm_stats_vec<bf16_t>)
@@ -338,7 +474,7 @@ hipError_t launch_norm_stats(const Tile3& t, shard_dtype_t dt, const void* tile,
                  : reinterpret_cast<const void*>(&norm_stats_elem<float>);
     hipError_t e = hipLaunchKernel(fn, dim3(blocks), dim3(kT), args, 0, s);
     if (e != hipSuccess) return e;
-    return hipLaunchKernel(reinterpret_cast<const void*>(&norm_stats_final), dim3(unsigned(a.n * a.G)), dim3(kT),
+    return hipLaunchKernel(reinterpret_cast<const void*>(&norm_stats_final), dim3(unsigned(a.n * a.G)), dim3(kF),
                            args, 0, s);
 }
 
@@ -356,16 +492,15 @@ hipError_t launch_norm_apply(const Tile3& t, shard_dtype_t dt, const void* tile,
     a.count = count;
     a.eps = eps;
     void* args[] = {&a};
+    if (vec_path(t, tile, out)) {
+        plan_vectors(a, t.esz, kApplyBlocks);
+        const void* fn = dt == SHARD_BF16 ? reinterpret_cast<const void*>(&norm_apply_vec<bf16_t>)
+                                          : reinterpret_cast<const void*>(&norm_apply_vec<float>);
+        return hipLaunchKernel(fn, dim3(unsigned(a.n * a.B)), dim3(kT), args, 0, s);
+    }
     hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(&norm_affine), dim3(grid_of(a.n * a.c)), dim3(kT),
                                    args, 0, s);
     if (e != hipSuccess) return e;
-    if (vec_path(t, tile, out)) {
-        // about 2048 blocks in all, at most one per row
-        const int64_t chunks = std::max<int64_t>(1, std::min<int64_t>(a.rows, ceil_div(2048, a.n)));
-        const void* fn = dt == SHARD_BF16 ? reinterpret_cast<const void*>(&norm_apply_vec<bf16_t>)
-                                          : reinterpret_cast<const void*>(&norm_apply_vec<float>);
-        return hipLaunchKernel(fn, dim3(unsigned(a.n * chunks)), dim3(kT), args, 0, s);
-    }
     const void* fn = dt == SHARD_BF16 ? reinterpret_cast<const void*>(&norm_apply_elem<bf16_t>)
                                       : reinterpret_cast<const void*>(&norm_apply_elem<float>);
     return hipLaunchKernel(fn, dim3(grid_of(a.n * a.rows * a.ext[2] * a.c)), dim3(kT), args, 0, s);

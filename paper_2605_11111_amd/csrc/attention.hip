@@ -57,17 +57,18 @@ struct AttnArgs {
     float* o;
     float* lse;
     int32_t sq, sk;
-    int32_t nqt;       // 256-query tiles per (batch, head)
+    int32_t nqt;       // query tiles per (batch, head)
     uint32_t nblocks;  // batch * heads * nqt
     float c2;          // scale * log2 e
     int32_t first;
 };
 
-template <int D>
+// SPLIT: the two groups take the same 128 queries and half of the keys each (see launch_d)
+template <int D, bool SPLIT = false>
 struct AttnCfg {
     static constexpr int NW = 8;               // waves: group A (0-3) and group B (4-7)
     static constexpr int THREADS = 64 * NW;
-    static constexpr int QB = NW * 32;         // queries per workgroup, 32 per wave
+    static constexpr int QB = SPLIT ? 128 : 256;  // queries per workgroup, 32 per wave
     static constexpr int KB = 32;              // keys per block
     static constexpr int NC = D / 16;          // MFMA K steps over the head dim
     static constexpr int NDT = D / 32;         // 32-row head-dim tiles of O^T
@@ -76,8 +77,10 @@ struct AttnCfg {
     static constexpr int KV_BYTES = KB * ROWB; // one K or V block
     static constexpr int NLDW = KV_BYTES / 1024;  // wave loads (64 lanes x 16 B) per matrix per block
     static constexpr int STAGE = 2 * KV_BYTES;    // K block, then V block
-    static constexpr int LDS = 2 * STAGE;         // double buffered
-    static constexpr int PRE = 4;                 // fragment reads issued ahead, in (K, V, V) triples
+    static constexpr int BUFB = SPLIT ? 2 * STAGE : STAGE;  // a buffer: with SPLIT, one stage per group
+    // double buffered; with SPLIT group B's state passes through it at the end (m, l and D / 2 values a lane)
+    static constexpr int LDS = SPLIT ? 2 * BUFB + 4 * 64 * 8 : 2 * BUFB;
+    static constexpr int PRE = SPLIT && D == 128 ? 3 : 4;  // fragment reads issued ahead, in (K, V, V) triples
     static_assert(D == 64 || D == 128, "head dim 64 or 128");
     static_assert(NC == 2 * NDT, "one O^T MFMA per score MFMA");
 };
@@ -106,10 +109,10 @@ using ic = std::integral_constant<int, B>;
 // kinds of iteration k of the key loop (see the kernel)
 enum { kFirst, kFirstLast, kMid, kLast, kFinal };
 
-template <int D>
+template <int D, bool SPLIT>
 __global__ __launch_bounds__(512, 1) void attn_block(AttnArgs a)
 {
-    using C = AttnCfg<D>;
+    using C = AttnCfg<D, SPLIT>;
     extern __shared__ uint4 lds4[];
     char* lds = reinterpret_cast<char*>(lds4);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -120,7 +123,13 @@ __global__ __launch_bounds__(512, 1) void attn_block(AttnArgs a)
     const bool grp_a = wv < 4;
     const uint32_t L = uint32_t(xcd_remap(blockIdx.x, gridDim.x));
     const uint32_t bh = L / uint32_t(a.nqt), qt = L - bh * uint32_t(a.nqt);
-    const int qi = int(qt) * C::QB + wave * 32 + ln;  // this lane's query
+    const int qi = int(qt) * C::QB + (SPLIT ? wave & 3 : wave) * 32 + ln;  // this lane's query
+    // the group's key blocks: nkb of them from block kb0, keys below kend. With SPLIT group A
+    // has one block less where the number is odd: its last is masked as a whole.
+    const int nall = (a.sk + C::KB - 1) / C::KB;
+    const int nkb = SPLIT ? (nall + 1) / 2 : nall;
+    const int kb0 = SPLIT && !grp_a ? nall - nkb : 0;
+    const int kend = SPLIT && grp_a ? (nall - nkb) * C::KB : a.sk;
 
     // Q^T fragments (B operand of S^T): lane (g, n) holds q[n][16c + 8g .. + 8]
     uint4 qf[C::NC];
@@ -136,14 +145,35 @@ __global__ __launch_bounds__(512, 1) void attn_block(AttnArgs a)
     // k_slot/v_slot^-1 of that key. Iteration k stages K of block k + 1 and V of
     // block k (V runs one block behind: iteration k multiplies the probabilities
     // of block k - 1); blocks past the end load as zero.
-    const int64_t kv_bytes = int64_t(a.sk) * C::ROWB;
+    const int64_t kv_bytes = int64_t(a.sk) * C::ROWB, kv_end = SPLIT ? int64_t(kend) * C::ROWB : kv_bytes;
     const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<char*>(a.k) + int64_t(bh) * kv_bytes, short(0), int(uint32_t(kv_bytes)), 0x00020000);
+        const_cast<char*>(a.k) + int64_t(bh) * kv_bytes, short(0), int(uint32_t(kv_end)), 0x00020000);
     const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<char*>(a.v) + int64_t(bh) * kv_bytes, short(0), int(uint32_t(kv_bytes)), 0x00020000);
+        const_cast<char*>(a.v) + int64_t(bh) * kv_bytes, short(0), int(uint32_t(kv_end)), 0x00020000);
+    // SPLIT: a group's waves stage its own blocks; a wave's loads are 16 keys (4 KiB) apart, the
+    // slots' period. The buffers end at kend (below 2^31 bytes), so the range check masks by itself.
+    uint32_t lk = 0, lv = 0;
+    if constexpr (SPLIT) {
+        const int byte = (wv & 3) * 1024 + lane * 16;
+        const int r = byte / C::ROWB, sl = (byte % C::ROWB) / 16;
+        lk = uint32_t(r * C::ROWB + k_slot<D>(r, sl) * 16);
+        lv = uint32_t(r * C::ROWB + v_slot(r, sl) * 16);
+    }
     auto stage = [&](int kbk, int kbv, int buf) {
+        if constexpr (SPLIT) {
+            const uint32_t bk = kbk >= 0 ? uint32_t(kb0 + kbk) * C::KV_BYTES : 0x80000000u;
+            const uint32_t bv = kbv >= 0 ? uint32_t(kb0 + kbv) * C::KV_BYTES : 0x80000000u;
+#pragma unroll
+            for (int i = 0; i < C::NLDW; i += C::NW / 2) {
+                char* dst = lds + buf * C::BUFB + (wv >> 2) * C::STAGE + (wv & 3) * 1024 + i * 1024;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, SC_LDSA(dst), 16, lk + (bk + i * 1024u), 0, 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, SC_LDSA(dst + C::KV_BYTES), 16, lv + (bv + i * 1024u), 0,
+                                                         0, 0);
+            }
+            return;
+        }
         for (int i = wv; i < C::NLDW; i += C::NW) {
-            char* dst = lds + buf * C::STAGE + i * 1024;
+            char* dst = lds + buf * C::BUFB + i * 1024;
             const int byte = i * 1024 + lane * 16;
             const int r = byte / C::ROWB, sl = (byte % C::ROWB) / 16;
             const int kk = kbk * C::KB + r, kv = kbv * C::KB + r;
@@ -157,7 +187,8 @@ __global__ __launch_bounds__(512, 1) void attn_block(AttnArgs a)
     };
 
     f32x16_a o[C::NDT];
-    float m = -__builtin_inff(), l = 0.f, alpha = 1.f;
+    // SPLIT: a finite start, so that a group whose first keys all score -infinity counts them as nothing
+    float m = SPLIT ? -3.402823466e38f : -__builtin_inff(), l = 0.f, alpha = 1.f;
     bool resc = false;
 #pragma unroll
     for (int dt = 0; dt < C::NDT; ++dt)
@@ -167,7 +198,7 @@ __global__ __launch_bounds__(512, 1) void attn_block(AttnArgs a)
     // fragment read addresses in buffer 0 (buffer 1 is an immediate offset
     // away). K: lane (g, key n) reads unit 2c + g of its key, slot
     // (2c + g) ^ (n % UPR) = 2 (c ^ zh) + (g ^ zl) with zh = (n % UPR) / 2, zl = n % 2.
-    const uint32_t lds0 = lds_addr(lds);
+    const uint32_t lds0 = lds_addr(lds) + (SPLIT && !grp_a ? uint32_t(C::STAGE) : 0u);
     const int zk = ln & (C::UPR - 1);
     uint32_t kad[C::NC];
 #pragma unroll
@@ -182,7 +213,6 @@ __global__ __launch_bounds__(512, 1) void attn_block(AttnArgs a)
     const uint32_t vcom =
         lds0 + uint32_t((4 * (G >> 1) + (ii >> 2)) * C::ROWB + 16 * (vx ^ (2 * vy1)) + 8 * (ii & 1));
     const uint32_t ve0 = vcom + 64u * uint32_t(vyb), vo0 = vcom - 64u * uint32_t(vyb);
-    const int nkb = (a.sk + C::KB - 1) / C::KB;
 
     f32x16_a sc;            // scores of the block between its MFMA and VALU phases
     uint32_t pn[2][4];      // its probabilities, bf16, as the O^T MFMAs' B operand
@@ -208,8 +238,8 @@ __global__ __launch_bounds__(512, 1) void attn_block(AttnArgs a)
         uint2 vr[C::NC][2];
         auto issue = [&](auto j_c) {
             constexpr int j = decltype(j_c)::value, c = j / C::NDT, dt = j % C::NDT;
-            kf[j] = lds_read_b128<BUF * C::STAGE>(kad[j]);
-            constexpr int voff = BUF * C::STAGE + C::KV_BYTES + 16 * c * C::ROWB + 64 * dt;
+            kf[j] = lds_read_b128<BUF * C::BUFB>(kad[j]);
+            constexpr int voff = BUF * C::BUFB + C::KV_BYTES + 16 * c * C::ROWB + 64 * dt;
             vr[j][0] = lds_read_tr16_b64<voff>((dt & 1) ? vo0 : ve0);
             vr[j][1] = lds_read_tr16_b64<voff + 8 * C::ROWB>((dt & 1) ? vo0 : ve0);
         };
@@ -246,7 +276,7 @@ __global__ __launch_bounds__(512, 1) void attn_block(AttnArgs a)
     // start of the next MFMA phase.
     auto valu_phase = [&](int k, auto mask_c) {
         if (decltype(mask_c)::value) {
-            const int kleft = a.sk - k * C::KB;
+            const int kleft = kend - (kb0 + k) * C::KB;
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 if (8 * (r >> 2) + 4 * g + (r & 3) >= kleft) sc[r] = -__builtin_inff();
@@ -343,6 +373,39 @@ __global__ __launch_bounds__(512, 1) void attn_block(AttnArgs a)
     else
         run(std::false_type{});
 
+    if constexpr (SPLIT) {
+        // group B's state joins group A's (the same queries and rows, lane by lane)
+        float4* ob = reinterpret_cast<float4*>(lds) + (wv & 3) * (4 * C::NDT * 64) + lane;
+        float2* mb = reinterpret_cast<float2*>(lds + 2 * C::BUFB) + (wv & 3) * 64 + lane;
+        if (!grp_a) {
+#pragma unroll
+            for (int dt = 0; dt < C::NDT; ++dt)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    ob[(4 * dt + j) * 64] =
+                        make_float4(o[dt][4 * j], o[dt][4 * j + 1], o[dt][4 * j + 2], o[dt][4 * j + 3]);
+            *mb = make_float2(m, l);
+        }
+        __syncthreads();
+        if (!grp_a) return;
+        const float2 s = *mb;
+        const float mm = fmaxf(m, s.x);
+        const float fa = m == mm ? 1.f : __builtin_amdgcn_exp2f(m - mm);
+        const float fb = s.x == mm ? 1.f : __builtin_amdgcn_exp2f(s.x - mm);
+        m = mm;
+        l = l * fa + s.y * fb;
+#pragma unroll
+        for (int dt = 0; dt < C::NDT; ++dt)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float4 v = ob[(4 * dt + j) * 64];
+                o[dt][4 * j] = o[dt][4 * j] * fa + v.x * fb;
+                o[dt][4 * j + 1] = o[dt][4 * j + 1] * fa + v.y * fb;
+                o[dt][4 * j + 2] = o[dt][4 * j + 2] * fa + v.z * fb;
+                o[dt][4 * j + 3] = o[dt][4 * j + 3] * fa + v.w * fb;
+            }
+    }
+
     // epilogue: lane (g, n) holds head-dim rows 32dt + 8j + 4g + e (e < 4) of
     // query qi; merge with the stored state
     if (qi >= a.sq) return;
@@ -392,11 +455,11 @@ __global__ __launch_bounds__(256) void attn_empty_state(float* o, float* lse, in
     }
 }
 
-template <int D>
-hipError_t launch_d(int64_t bh, int64_t sq, int64_t sk, float scale, const void* q, const void* k, const void* v,
+template <int D, bool SPLIT>
+hipError_t launch_as(int64_t bh, int64_t sq, int64_t sk, float scale, const void* q, const void* k, const void* v,
                     float* o, float* lse, bool first, hipStream_t s)
 {
-    using C = AttnCfg<D>;
+    using C = AttnCfg<D, SPLIT>;
     AttnArgs a{};
     a.q = static_cast<const char*>(q);
     a.k = static_cast<const char*>(k);
@@ -409,12 +472,31 @@ hipError_t launch_d(int64_t bh, int64_t sq, int64_t sk, float scale, const void*
     a.nblocks = uint32_t(bh * a.nqt);
     a.c2 = scale * kLog2e;
     a.first = first ? 1 : 0;
-    auto fn = &attn_block<D>;
+    auto fn = &attn_block<D, SPLIT>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
                                        C::LDS);
     if (e != hipSuccess) return e;
     void* args[] = {&a};
     return hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3(a.nblocks), dim3(C::THREADS), args, C::LDS, s);
+}
+
+// Whole or split workgroups: one workgroup is resident per CU, so a launch takes
+// rounds of 256, and a workgroup's time is its key blocks (a split one's join about four
+// more). The split halves the keys of a workgroup and doubles their number: it wins where
+// whole workgroups leave CUs idle: four blocks of 16 x 2044 x 2044 x 128 (128 whole
+// workgroups) 243.4 us whole, 170.7 us split. Its fragment reads run three triples ahead, not
+// four, at head dim 128: four spilled registers.
+// A split's masked block multiplies -infinity by the scale: only a positive one keeps it.
+template <int D>
+hipError_t launch_d(int64_t bh, int64_t sq, int64_t sk, float scale, const void* q, const void* k, const void* v,
+                    float* o, float* lse, bool first, hipStream_t s)
+{
+    constexpr int64_t kCUs = 256;
+    const int64_t blocks = (sk + 31) / 32, whole = bh * ((sq + 255) / 256), half = bh * ((sq + 127) / 128);
+    const bool split = blocks > 1 && scale > 0.f && half < (int64_t(1) << 31) && sk * D * 2 < (int64_t(1) << 31) - 65536 &&
+                       (half + kCUs - 1) / kCUs * ((blocks + 1) / 2 + 4) < (whole + kCUs - 1) / kCUs * blocks;
+    return split ? launch_as<D, true>(bh, sq, sk, scale, q, k, v, o, lse, first, s)
+                 : launch_as<D, false>(bh, sq, sk, scale, q, k, v, o, lse, first, s);
 }
 
 }  // namespace
